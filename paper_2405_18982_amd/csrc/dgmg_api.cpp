@@ -87,11 +87,24 @@ void fill_tab(int dim, const dgmg::HostTables& H, std::vector<unsigned char>& ou
   // inverse eigenvalue sums, summed in the kernels' former order, in FP64
   const std::vector<double>* lams[3] = {H.lam, H.lamf, H.lamc};
   auto inv = [](double s) { return std::isinf(s) ? 0.0 : 1.0 / s; };
+  // (qy, qz) of the direct smoother's x-lines in the order of its lanes, cell by cell
+  constexpr int n = K + 1;
+  int ql[E * E][2];
+  for (int l = 0; l < E * E; ++l) {
+    const int cell = l / (n * n), in = l % (n * n);
+    ql[l][0] = (cell & 1) * n + in % n;
+    ql[l][1] = (cell >> 1) * n + in / n;
+  }
   for (int sp = 0; sp < 3; ++sp)
     for (int tx = 0; tx < 4; ++tx)
       for (int ty = 0; ty < 4; ++ty) {
         const std::vector<double>& lx = lams[sp][tx];
         const std::vector<double>& ly = lams[sp][ty];
+        if (sp == 0 && dim == 2 && dgmg::direct_smoother(2, K)) {
+          for (int qx = 0; qx < E; ++qx)
+            for (int qy = 0; qy < E; ++qy) t->rs[0][tx * 4 + ty][qx * E + qy] = (T)inv(lx[qx] + ly[qy]);
+          continue;
+        }
         if (dim == 2) {
           T* r = t->rs[sp][tx * 4 + ty];
           for (int qy = 0; qy < E; ++qy)
@@ -101,6 +114,11 @@ void fill_tab(int dim, const dgmg::HostTables& H, std::vector<unsigned char>& ou
         for (int tz = 0; tz < 4; ++tz) {
           const std::vector<double>& lz = lams[sp][tz];
           T* r = t->rs[sp][(tx * 4 + ty) * 4 + tz];
+          if (sp == 0 && dgmg::direct_smoother(3, K)) {
+            for (int qx = 0; qx < E; ++qx)
+              for (int l = 0; l < E * E; ++l) r[qx * E * E + l] = (T)inv(ly[ql[l][0]] + (lx[qx] + lz[ql[l][1]]));
+            continue;
+          }
           for (int qz = 0; qz < E; ++qz)
             for (int qx = 0; qx < E; ++qx)
               for (int qy = 0; qy < E; ++qy) r[(qz * E + qx) * E + qy] = (T)inv(ly[qy] + (lx[qx] + lz[qz]));
@@ -113,6 +131,12 @@ void fill_tab(int dim, const dgmg::HostTables& H, std::vector<unsigned char>& ou
     // kernels' reciprocal (estimate + Newton steps) returns ~0 without NaNs
     for (int i = 0; i < E; ++i)
       t->lam[ty][i] = std::isinf(H.lam[ty][i]) ? (T)(sizeof(T) == 8 ? 1e300 : 1e30) : (T)H.lam[ty][i];
+    for (int i = 0; i < E * E; ++i) t->MS[ty][i] = (T)H.MS[ty][i];
+    for (int i = 0; i < E; ++i) {
+      t->gp[ty][i] = (T)H.gp[ty][i];
+      t->gt[ty][i] = (T)H.gt[ty][i];
+      t->gm[ty][i] = (T)H.gm[ty][i];
+    }
     for (int i = 0; i < E * E; ++i) t->Sf[ty][i] = (T)H.Sf[ty][i];
     for (int i = 0; i < E; ++i) t->lamf[ty][i] = (T)H.lamf[ty][i];
     for (int i = 0; i < E * E; ++i) t->Sc[ty][i] = (T)H.Sc[ty][i];
@@ -262,6 +286,7 @@ PatchGrid grid_colour0(const dgmg_ctx* c, int N) {
     g.off[i] = 0;
     g.npatch *= g.cnt[i];
   }
+  dgmg::grid_magic(g);
   return g;
 }
 
@@ -290,6 +315,7 @@ PatchGrid grid_colour(const dgmg_ctx* c, int N, int colour, bool tiling = false)
     }
     g.npatch *= g.cnt[i];
   }
+  dgmg::grid_magic(g);
   return g;
 }
 
@@ -1357,10 +1383,10 @@ dgmg_status tune_kernel(dgmg_ctx* c, int nrhs, bool smooth, int level, T* x, T* 
   const KernelSet<T>& ks = kset<T>(c);
   const bool rpack = nrhs > 1 && (smooth ? ks.smooth_rpack : ks.apply_rpack);
   if (smooth) {
-    const bool hi = c->variant == DGMG_SMOOTH_FULL ? ks.smooth_hi_full : ks.smooth_split;
-    for (int v = 0; v < (hi ? 8 : 4); ++v) shapes.push_back(v);
-    if (rpack)
-      for (int v = 8; v < 12; ++v) shapes.push_back(v);
+    const bool hi = c->variant == DGMG_SMOOTH_CLAMPED ? ks.smooth_split : ks.smooth_hi_full;
+    const bool direct = ks.smooth_direct && (c->variant == DGMG_SMOOTH_EXACT || c->variant == DGMG_SMOOTH_LOCAL);
+    for (int v = 0; v < 12; ++v)
+      if ((v < 8 ? v < 4 || hi : rpack) && !(direct && (v & 2))) shapes.push_back(v);
   } else {
     shapes = {0, 1};
     if (ks.apply_rf) shapes.push_back(2);

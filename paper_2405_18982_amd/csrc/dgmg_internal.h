@@ -17,6 +17,14 @@ constexpr int kApplyShapes = 4;
 // right-hand sides of one patch per workgroup (two slot counts) x prefetch
 constexpr int kSmoothShapes = 12;
 
+// Where the Dirichlet smoothers take the direct form (one solve for the new
+// values) and not a residual by operator passes.  On the shortest lines its
+// face passes outweigh the operator passes they replace: a smoothing step of
+// 3-D Q1 takes 33.1 us on 8^3 cells and 105.6 us on 64^3 by operator passes, 36.7
+// and 109.4 us directly; 2-D Q2 on 8^2 cells 16.4 against 17.6 us, 2-D Q3 on 64^2
+// (three right-hand sides) 21.3 both, 2-D Q7 on 128^2 53.0 against 40.3 us.
+constexpr bool direct_smoother(int dim, int k) { return dim == 3 ? k >= 2 : k >= 4; }
+
 // Reference (h = 1, kappa = 1) data of Q_K on a two-cell patch that depends
 // on the penalty, in the arithmetic type T of the kernels that read them.
 // Built on the host in FP64 (setup.cpp) and uploaded once per context.  (The
@@ -26,15 +34,21 @@ constexpr int kSmoothShapes = 12;
 //   S[t], lam[t] : fast-diagonalisation eigenpairs of patch type t on the
 //         Dirichlet local space, padded to E (unused eigenvalue slots hold a
 //         huge finite value)
+//   MS[t], gp[t], gt[t], gm[t] : S^T M and the couplings of the Dirichlet space
+//         to the dropped end nodes and the outer traces in the eigenbasis
+//         (dgmg_setup.h)
 //   Sf[t], lamf[t] : the same on the whole patch (Full kernel)
 //   Sc[t], lamc[t] : C S on the clamped space with basis C (clamped kernel)
 //   rs[s][c] : the inverse eigenvalue sums of the fast-diagonalisation solve
 //         of local space s (0 Dirichlet, 1 whole patch, 2 clamped) for the
-//         patch-type combination c, computed in FP64 and rounded: in 3-D,
-//         c = (tx 4 + ty) 4 + tz and rs[s][c][(qz E + qx) E + qy] =
-//         1 / (lam_y[qy] + (lam_x[qx] + lam_z[qz])); in 2-D, c = tx 4 + ty and
-//         rs[s][c][qy E + qx] = 1 / (lam_x[qx] + lam_y[qy]); 0 where a slot is
-//         unused
+//         patch-type combination c = (tx 4 + ty) 4 + tz (2-D: tx 4 + ty),
+//         computed in FP64 and rounded; 0 where a slot is unused:
+//         rs[s][c][(qz E + qx) E + qy], in 2-D rs[s][c][qy E + qx].
+//         s = 0 with the direct smoother, for lanes that hold x-lines:
+//         rs[0][c][qx E^2 + l] of the x-line (qy, qz) of lane l, the lanes
+//         running through the plane cell by cell (qy = (l' mod 2) n + i mod n,
+//         qz = (l' div 2) n + i div n with l' = l div n^2, i = l mod n^2); in
+//         2-D rs[0][c][qx E + qy].
 template <int K, typename T>
 struct Tab {
   static constexpr int n = K + 1;
@@ -42,6 +56,10 @@ struct Tab {
   T sigma;
   T S[4][E * E];
   T lam[4][E];
+  T MS[4][E * E];
+  T gp[4][E];
+  T gt[4][E];
+  T gm[4][E];
   T Sf[4][E * E];
   T lamf[4][E];
   T Sc[4][E * E];
@@ -60,7 +78,20 @@ struct PatchGrid {
   int npatch;  // product of cnt
   int xcd_remap;  // 1: give each XCD a contiguous range of patches
   int nrhs;    // right-hand sides of the launch (set by the launchers)
+  // multipliers of the divisions by cnt[0], cnt[1] (grid_magic; 0: divide)
+  unsigned mul[2];
 };
+
+// r / cnt = (r * mul) >> 32 with mul = ceil(2^32 / cnt), exact while
+// r (mul cnt - 2^32) < 2^32, hence for r < npatch if npatch cnt <= 2^32.  A
+// true division by a launch argument is a chain of some forty instructions
+// at the start of every patch.
+inline void grid_magic(PatchGrid& g) {
+  for (int i = 0; i < 2; ++i) {
+    const bool ok = g.cnt[i] > 1 && (unsigned long long)g.npatch * (unsigned)g.cnt[i] <= (1ull << 32);
+    g.mul[i] = ok ? (unsigned)(((1ull << 32) + (unsigned)g.cnt[i] - 1) / (unsigned)g.cnt[i]) : 0u;
+  }
+}
 
 // Host-visible launchers of one (D, K) instantiation.  All vectors are
 // [nrhs][ndof] device arrays; `tab` points to a device Tab<K, T>.
@@ -90,6 +121,9 @@ struct KernelSet {
   // the Full kernel
   int smooth_split;
   int smooth_hi_full;
+  // 1 where the Dirichlet smoothers take the direct form, which has neither
+  // prefetch shapes nor two-wave shapes
+  int smooth_direct;
   hipError_t (*restrict_residual)(const void* tab, PatchGrid g, T scale, const T* x, const T* b,
                                   T* bc, int nrhs, long long ndof, long long ndof_c,
                                   hipStream_t s);

@@ -127,12 +127,33 @@ constexpr EOCell make_eo_cell(const double (&B)[n * n]) {
   return r;
 }
 static constexpr EOCell kEOM = make_eo_cell(kRef.M);
+// The same for FP32, each half-sum and half-difference pair on a grid (2^-24 of
+// the next power of two above |A| + |Bo|) on which A + Bo and A - Bo are exact in
+// FP32: the rows of M and the even-odd form then stand for one matrix.
+constexpr EOCell grid_eo_cell(EOCell c) {
+  for (int i = 0; i < kHN * kHN; ++i) {
+    const double m = (c.A[i] < 0 ? -c.A[i] : c.A[i]) + (c.Bo[i] < 0 ? -c.Bo[i] : c.Bo[i]);
+    double q = 1.0;
+    while (q > m) q *= 0.5;
+    q *= 2.0 / 16777216.0;
+    for (double* x : {&c.A[i], &c.Bo[i]}) *x = (double)(long long)(*x / q + (*x < 0 ? -0.5 : 0.5)) * q;
+  }
+  return c;
+}
+static constexpr EOCell kEOMq = grid_eo_cell(kEOM);
 static constexpr EOCell kEOL = make_eo_cell(kRef.Lcons);
+static constexpr EOCell kEOK = make_eo_cell(kRef.Ks);
+
+// The line's mass by even-odd halves; in 2-D FP32 by plain rows, in the very
+// operations that contract the face data (face_dot), where arithmetic does not
+// bound the kernels.
+template <typename T>
+constexpr bool kEOMass = kEOC && !(D == 2 && sizeof(T) == 4);
 
 // bl = B w for the cell c of patch line v (MASS: B = M, else Lcons)
 template <typename T, bool MASS>
 __device__ __forceinline__ void cell_eo(const Line<T>& v, int c, T (&bl)[n]) {
-  constexpr const EOCell& C = MASS ? kEOM : kEOL;
+  constexpr const EOCell& C = !MASS ? kEOL : sizeof(T) == 4 ? kEOMq : kEOM;
   T ve[kHN], vo[kHN];
 #pragma unroll
   for (int j = 0; j < kHN; ++j) {
@@ -164,7 +185,7 @@ __device__ __forceinline__ void cell_eo(const Line<T>& v, int c, T (&bl)[n]) {
 template <typename T>
 __device__ __forceinline__ void line_mass(const Tab<K, T>* __restrict__ t, const Line<T>& v, Line<T>& o,
                                           bool need0 = true, bool needE = true) {
-  if constexpr (kEOC) {
+  if constexpr (kEOMass<T>) {
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
       T bl[n];
@@ -215,11 +236,153 @@ struct Sides {
   bool lit;
 };
 
+// FP32 evaluates the 1-D operator on differences: stiffness and end derivatives
+// of a cell act on its values less one of them (their rows sum to zero, so a
+// column drops out), the face terms on jumps.  With the values themselves the
+// rounding of the coefficients acts like a small reaction term: the FP32
+// V-cycles of Q5..Q7 on random loads were off by 1e-6..4e-5.  FP64 keeps the
+// plain rows.
+template <typename T>
+constexpr bool kDiff = sizeof(T) == 4;
+
+// alpha of a face from the neighbour's derivative g and trace tr; on
+// differences the penalty part is left to the line, which forms the jump
+template <typename T, int SIDE>
+__device__ __forceinline__ T face_alpha(T sg, T g, T tr) {
+  const T half = T(0.5);
+  if constexpr (kDiff<T>) return SIDE == 0 ? half * g : -half * g;
+  else return SIDE == 0 ? (half * g - sg * tr) : (-sg * tr - half * g);
+}
+// end derivative (SIDE 0: d1, the neighbour below; 1: d0, above) of the n
+// values w(j) of a neighbour's line
+template <typename T, int SIDE, typename W>
+__device__ __forceinline__ T face_grad(W w) {
+  T g = T(0);
+  if constexpr (kDiff<T>) {
+    const T w0 = w(0);
+#pragma unroll
+    for (int j = 1; j < n; ++j) g += (SIDE == 0 ? T(kRef.d1[j]) : T(kRef.d0[j])) * (w(j) - w0);
+  } else {
+#pragma unroll
+    for (int j = 0; j < n; ++j) g += (SIDE == 0 ? T(kRef.d1[j]) : T(kRef.d0[j])) * w(j);
+  }
+  return g;
+}
+// end derivatives of cell c of a line (at its left and right end), on
+// differences: the even and odd parts serve both
+template <typename T>
+__device__ __forceinline__ void cell_grad(const Line<T>& v, int c, T& g0, T& g1) {
+  const T ref = kOddN ? v.v[c * n + kHN] + v.v[c * n + kHN] : v.v[c * n] + v.v[c * n + n - 1];
+  T e = T(0), o = T(0);
+#pragma unroll
+  for (int j = kOddN ? 0 : 1; j < kHN; ++j)
+    e += T(0.5 * (kRef.d0[j] + kRef.d0[n - 1 - j])) * ((v.v[c * n + j] + v.v[c * n + n - 1 - j]) - ref);
+#pragma unroll
+  for (int j = 0; j < kHN; ++j)
+    o += T(0.5 * (kRef.d0[j] - kRef.d0[n - 1 - j])) * (v.v[c * n + j] - v.v[c * n + n - 1 - j]);
+  g0 = o + e;
+  g1 = o - e;
+}
+// stiffness rows of cell c of a line, on differences
+template <typename T>
+__device__ __forceinline__ void cell_stiff(const Line<T>& v, int c, T (&bl)[n]) {
+  const T ref = kOddN ? v.v[c * n + kHN] + v.v[c * n + kHN] : v.v[c * n] + v.v[c * n + n - 1];
+  T ve[kHN], vo[kHN];
+#pragma unroll
+  for (int j = 0; j < kHN; ++j) {
+    ve[j] = (v.v[c * n + j] + v.v[c * n + n - 1 - j]) - ref;
+    vo[j] = v.v[c * n + j] - v.v[c * n + n - 1 - j];
+  }
+#pragma unroll
+  for (int mu = 0; mu < kHN; ++mu) {
+    T se = T(0), so = T(0);
+#pragma unroll
+    for (int j = kOddN ? 0 : 1; j < kHN; ++j) se += T(kEOK.A[mu * kHN + j]) * ve[j];
+#pragma unroll
+    for (int j = 0; j < kHN; ++j) so += T(kEOK.Bo[mu * kHN + j]) * vo[j];
+    bl[mu] = se + so;
+    bl[n - 1 - mu] = se - so;
+  }
+  if constexpr (kOddN) {
+    T sm = T(0);
+#pragma unroll
+    for (int j = 0; j < kHN; ++j) sm += T(kEOK.rowm[j]) * ve[j];
+    bl[kHN] = sm;
+  }
+}
+// The face at the outer left (SIDE 0) or right end of a patch line, on
+// differences: what it adds to the end row (end) and the factor of d0 (d1) it
+// adds to the rows of its cell (cf); v0: the line's end value, g: the line's
+// derivative there.
+template <typename T, int SIDE>
+__device__ __forceinline__ void outer_face(T sg, const Sides<T>& sd, T v0, T g, T& end, T& cf) {
+  const T half = T(0.5);
+  const bool bnd = SIDE == 0 ? sd.bl : sd.br;
+  const T gs = SIDE == 0 ? g : -g;
+  if (bnd) {  // Nitsche: no value beyond
+    end = sg * v0 + gs;
+    cf = SIDE == 0 ? v0 : -v0;
+  } else if (sd.lit) {
+    end = sg * v0 + half * gs;
+    cf = T(0);
+  } else {
+    const T jump = SIDE == 0 ? v0 + (sd.bL + sd.bL) : v0 - (sd.bR + sd.bR);  // own less the neighbour's
+    end = sg * jump + ((SIDE == 0 ? sd.aL : sd.aR) + half * gs);
+    cf = SIDE == 0 ? half * jump : -half * jump;
+  }
+}
+// rows of cell C of the patch line v, on differences
+template <typename T, int C, bool ACC>
+__device__ __forceinline__ void cell_sipg_diff(T sg, const Line<T>& v, const Sides<T>& sd, T (&o)[n], bool need0,
+                                               bool needE) {
+  const T half = T(0.5);
+  T g00, g01, g10, g11, bl[n];
+  cell_grad<T>(v, 0, g00, g01);
+  cell_grad<T>(v, 1, g10, g11);
+  cell_stiff<T>(v, C, bl);
+  // the face between the two cells
+  const T jump = v.v[n - 1] - v.v[n];
+  const T mid = sg * jump - half * (g01 + g10);
+  T end, cf;
+  if constexpr (C == 0) outer_face<T, 0>(sg, sd, v.v[0], g00, end, cf);
+  else outer_face<T, 1>(sg, sd, v.v[E - 1], g11, end, cf);
+  const T c0 = C == 0 ? cf : -half * jump;  // factor of d0 (left face of the cell)
+  const T c1 = C == 0 ? -half * jump : cf;  // factor of d1
+#pragma unroll
+  for (int mu = 0; mu < n; ++mu) {
+    if ((C == 0 && mu == 0 && !need0) || (C == 1 && mu == n - 1 && !needE)) continue;
+    T s = ACC ? o[mu] : T(0);
+    s += bl[mu];
+    if (mu == 0) s += C == 0 ? end : -mid;
+    if (mu == n - 1) s += C == 0 ? mid : end;
+    s += T(kRef.d0[mu]) * c0 + T(kRef.d1[mu]) * c1;
+    o[mu] = s;
+  }
+}
+
 // o (+)= 1-D SIPG of the patch line v; the end outputs only when need0 / needE
 template <typename T, bool ACC>
 __device__ __forceinline__ void line_sipg(const Tab<K, T>* __restrict__ t, const Line<T>& v,
                                           const Sides<T>& sd, Line<T>& o, bool need0 = true,
                                           bool needE = true) {
+  if constexpr (kDiff<T>) {
+    T lo[n], hi[n];
+    if constexpr (ACC) {
+#pragma unroll
+      for (int mu = 0; mu < n; ++mu) {
+        lo[mu] = o.v[mu];
+        hi[mu] = o.v[n + mu];
+      }
+    }
+    cell_sipg_diff<T, 0, ACC>(t->sigma, v, sd, lo, need0, needE);
+    cell_sipg_diff<T, 1, ACC>(t->sigma, v, sd, hi, need0, needE);
+#pragma unroll
+    for (int mu = 0; mu < n; ++mu) {
+      if (mu > 0 || need0) o.v[mu] = lo[mu];
+      if (mu < n - 1 || needE) o.v[n + mu] = hi[mu];
+    }
+    return;
+  }
   const T sg = t->sigma;
   const T half = T(0.5);
 #pragma unroll
@@ -305,6 +468,20 @@ template <> struct FDB<SP_CLAMPED, 1> { static constexpr int PLO = 0, PHI = E - 
 template <> struct FDB<SP_CLAMPED, 2> { static constexpr int PLO = 1, PHI = E, QN = E - 2; };
 template <> struct FDB<SP_CLAMPED, 3> { static constexpr int PLO = 0, PHI = E, QN = E; };
 
+// The 1-D data of one pass.  OPQ: through a pointer the compiler cannot connect
+// with other passes' reads of the same table.  Otherwise it keeps the
+// coefficients of one pass (up to E^2) for the next in scalar registers it
+// does not have, and every pass spends more instructions on spilling them to
+// vector lanes than on arithmetic.  Constant address space: scalar loads.
+template <typename T>
+using Coef = const T __attribute__((address_space(4)))*;
+template <typename T, bool OPQ>
+__device__ __forceinline__ Coef<T> pass_coef(const T* p) {
+  unsigned long long a = (unsigned long long)p;
+  if constexpr (OPQ) asm volatile("" : "+s"(a));
+  return (Coef<T>)a;
+}
+
 template <typename T, int SP>
 __device__ __forceinline__ const T* fd_S(const Tab<K, T>* __restrict__ t, int ty) {
   return SP == SP_FULL ? t->Sf[ty] : SP == SP_CLAMPED ? t->Sc[ty] : t->S[ty];
@@ -335,7 +512,7 @@ __device__ __forceinline__ void load_rs(const Tab<K, T>* __restrict__ t, const i
 // from Q4 on: measured on a smoothing step, 4-12% faster for Q4..Q7, 4-5%
 // slower for Q3 (h = 3), where the dense contraction stays.
 constexpr int kEOH = n - 1;
-constexpr bool kEO = (K >= 4);
+constexpr bool kEO = (K >= 2);
 
 template <typename T>
 __device__ __forceinline__ void eo_split(const Line<T>& v, T (&vp)[kEOH], T (&vm)[kEOH]) {
@@ -347,7 +524,7 @@ __device__ __forceinline__ void eo_split(const Line<T>& v, T (&vp)[kEOH], T (&vm
 }
 // coefficient q < 2h of S^T v
 template <typename T>
-__device__ __forceinline__ T eo_coef(const T* S, const T (&vp)[kEOH], const T (&vm)[kEOH], int q) {
+__device__ __forceinline__ T eo_coef(Coef<T> S, const T (&vp)[kEOH], const T (&vm)[kEOH], int q) {
   T s = T(0);
 #pragma unroll
   for (int k = 0; k < kEOH; ++k) s += S[(1 + k) * E + q] * (q < kEOH ? vp[k] : vm[k]);
@@ -355,7 +532,7 @@ __device__ __forceinline__ T eo_coef(const T* S, const T (&vp)[kEOH], const T (&
 }
 // even and odd parts of the outputs at nodes 1 + k and E - 2 - k of S v
 template <typename T>
-__device__ __forceinline__ void eo_pair(const T* S, const Line<T>& v, int k, T& e, T& d) {
+__device__ __forceinline__ void eo_pair(Coef<T> S, const Line<T>& v, int k, T& e, T& d) {
   T se = T(0), sd = T(0);
 #pragma unroll
   for (int q = 0; q < kEOH; ++q) se += S[(1 + k) * E + q] * v.v[q];
@@ -365,11 +542,21 @@ __device__ __forceinline__ void eo_pair(const T* S, const Line<T>& v, int k, T& 
   d = sd;
 }
 
+// Which spaces' contractions read S opaquely (pass_coef): all of the Dirichlet
+// space; of the larger ones those whose table does not fit the scalar
+// registers and whose patch type the compiler knows to be uniform in a wave --
+// elsewhere it reads the types' tables ahead of the diverging branches, and
+// that is worth more (smoothing steps of the Full kernel on 32^3, opaque
+// against not: Q7 FP32 726 / 1322 us, Q3 FP64 156 / 185 us, but Q2 FP64 189 /
+// 173 us, Q4 FP64 1002 / 924 us).
+template <typename T, int SP>
+constexpr bool kOpaqueFD = SP == SP_DIR || (TPP % 64 == 0 && E * E * (int)sizeof(T) > 4 * 100);
+
 // o[q] = sum_p S[p][q] v[p]
 template <typename T, int TY, int SP>
 __device__ __forceinline__ void line_St_t(const Tab<K, T>* __restrict__ t, const Line<T>& v, Line<T>& o) {
   using B = FDB<SP, TY>;
-  const T* S = fd_S<T, SP>(t, TY);
+  const Coef<T> S = pass_coef<T, kOpaqueFD<T, SP>>(fd_S<T, SP>(t, TY));
   if constexpr (kEO && SP == SP_DIR && TY == 0) {
     T vp[kEOH], vm[kEOH];
     eo_split<T>(v, vp, vm);
@@ -391,7 +578,7 @@ __device__ __forceinline__ void line_St_t(const Tab<K, T>* __restrict__ t, const
 template <typename T, int TY, int SP>
 __device__ __forceinline__ void line_S_t(const Tab<K, T>* __restrict__ t, const Line<T>& v, Line<T>& o) {
   using B = FDB<SP, TY>;
-  const T* S = fd_S<T, SP>(t, TY);
+  const Coef<T> S = pass_coef<T, kOpaqueFD<T, SP>>(fd_S<T, SP>(t, TY));
   if constexpr (kEO && SP == SP_DIR && TY == 0) {
     // outputs written in increasing node order, as in the other types: the
     // compiler then merges the four type branches' stores into one line
@@ -461,13 +648,14 @@ __device__ __forceinline__ int slot_of() {
 // for PPB consecutive right-hand sides, so that every slot of the workgroup
 // has the same patch type and position (uniform branches and scalar loads of
 // the 1-D data where slots share a wave); slots past the last right-hand side
-// get an out-of-range patch index and only meet the barriers.
+// get an out-of-range patch index, npatch more than the others', and only meet
+// the barriers.
 template <int PPB, bool RP>
 __device__ __forceinline__ void slot_work(const PatchGrid& g, int slot, int& pid, int& rhs) {
   const int blk = xcd_block(blockIdx.x, gridDim.x, g.xcd_remap);
   if constexpr (RP) {
     rhs = (int)blockIdx.y * PPB + slot;
-    pid = rhs < g.nrhs ? blk : g.npatch;
+    pid = rhs < g.nrhs ? blk : blk + g.npatch;
     if (rhs >= g.nrhs) rhs = 0;
   } else {
     pid = blk * PPB + slot;
@@ -486,8 +674,11 @@ __device__ __forceinline__ PatchPos patch_pos(const PatchGrid& g, int pid) {
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     if (i < D) {
-      const int m = r % g.cnt[i];
-      r /= g.cnt[i];
+      // r / cnt by the launch's multiplier (grid_magic); the last quotient is 0
+      int quo = 0;
+      if (i < D - 1) quo = g.mul[i] ? (int)__umulhi((unsigned)r, g.mul[i]) : r / g.cnt[i];
+      const int m = r - quo * g.cnt[i];
+      r = quo;
       P.lo[i] = g.off[i] + 2 * m;
       const int v = P.lo[i] + 1;  // the patch's vertex
       P.ty[i] = (v == 1 ? 1 : 0) | (v == g.N - 1 ? 2 : 0);
@@ -531,18 +722,12 @@ __device__ __forceinline__ Sides<T> xsides_rows(T sg, bool bl, bool br, const T 
   if (!sd.bl) {
     const T tr = rl[K];
     sd.bL = -half * tr;
-    T g = T(0);
-#pragma unroll
-    for (int j = 0; j < n; ++j) g += T(kRef.d1[j]) * rl[j];
-    sd.aL = half * g - sg * tr;
+    sd.aL = face_alpha<T, 0>(sg, face_grad<T, 0>([&](int j) { return rl[j]; }), tr);
   }
   if (!sd.br) {
     const T tr = rr[0];
     sd.bR = half * tr;
-    T g = T(0);
-#pragma unroll
-    for (int j = 0; j < n; ++j) g += T(kRef.d0[j]) * rr[j];
-    sd.aR = -sg * tr - half * g;
+    sd.aR = face_alpha<T, 1>(sg, face_grad<T, 1>([&](int j) { return rr[j]; }), tr);
   }
   return sd;
 }
@@ -566,23 +751,13 @@ __device__ __forceinline__ Sides<T> xline_sides(const Tab<K, T>* __restrict__ t,
       const T* r = x + row0 - NC;
       const T tr = r[K];
       sd.bL = -half * tr;
-      if (MODE == 0) {
-        T g = T(0);
-#pragma unroll
-        for (int j = 0; j < n; ++j) g += T(kRef.d1[j]) * r[j];
-        sd.aL = half * g - sg * tr;
-      }
+      if (MODE == 0) sd.aL = face_alpha<T, 0>(sg, face_grad<T, 0>([&](int j) { return r[j]; }), tr);
     }
     if (!sd.br) {
       const T* r = x + row0 + 2 * NC;
       const T tr = r[0];
       sd.bR = half * tr;
-      if (MODE == 0) {
-        T g = T(0);
-#pragma unroll
-        for (int j = 0; j < n; ++j) g += T(kRef.d0[j]) * r[j];
-        sd.aR = -sg * tr - half * g;
-      }
+      if (MODE == 0) sd.aR = face_alpha<T, 1>(sg, face_grad<T, 1>([&](int j) { return r[j]; }), tr);
     }
   }
   return sd;
@@ -627,10 +802,9 @@ __device__ __forceinline__ void gather_ext(const Tab<K, T>* __restrict__ t, cons
       const T tr = x[base + (long long)((side == 0) ? K : 0) * strideN];
       beta = (side == 0) ? -half * tr : half * tr;
       if (MODE == 0) {
-        T g = T(0);
-#pragma unroll
-        for (int j = 0; j < n; ++j) g += ((side == 0) ? T(kRef.d1[j]) : T(kRef.d0[j])) * x[base + (long long)j * strideN];
-        alpha = (side == 0) ? (half * g - sg * tr) : (-sg * tr - half * g);
+        auto w = [&](int j) { return x[base + (long long)j * strideN]; };
+        alpha = (side == 0) ? face_alpha<T, 0>(sg, face_grad<T, 0>(w), tr)
+                            : face_alpha<T, 1>(sg, face_grad<T, 1>(w), tr);
       }
     }
     if (NCOMP == 2) {
@@ -663,27 +837,57 @@ __device__ __forceinline__ void mass_row(int mu, T (&row)[n]) {
   for (int nu = 0; nu < n; ++nu) row[nu] = kMassRows<T>.v[mu * n + nu];
 }
 
+// The mass row that contracts the neighbours' face data: M as the line's own
+// mass has it (line_mass), or the two sides' rounding of M would become a jump
+// that the penalty multiplies.
+template <typename T>
+constexpr MassRows<T> make_face_rows() {
+  MassRows<T> r = make_mass_rows<T>();
+  if (kEOMass<T> && sizeof(T) == 4)
+    for (int mu = 0; mu < n; ++mu) {
+      const int m = mu < n - 1 - mu ? mu : n - 1 - mu;
+      for (int j = 0; j < kHN; ++j) {
+        const bool mid = kOddN && mu == kHN;
+        const double e = mid ? kEOMq.rowm[j] : kEOMq.A[m * kHN + j];
+        const double o = mid ? 0.0 : mu == m ? kEOMq.Bo[m * kHN + j] : -kEOMq.Bo[m * kHN + j];
+        r.v[mu * n + j] = T(e + o);
+        r.v[mu * n + n - 1 - j] = T(e - o);
+      }
+      if (kOddN) r.v[mu * n + kHN] = T(mu == kHN ? kEOMq.rowm[kHN] : kEOMq.colm[m]);
+    }
+  return r;
+}
+template <typename T>
+__device__ constexpr MassRows<T> kFaceRows = make_face_rows<T>();
+template <typename T>
+__device__ __forceinline__ void face_row(int mu, T (&row)[n]) {
+#pragma unroll
+  for (int nu = 0; nu < n; ++nu) row[nu] = kFaceRows<T>.v[mu * n + nu];
+}
+// sum_nu M[mu][nu] w(nu) for the row of mu
+template <typename T, typename W>
+__device__ __forceinline__ T face_dot(const T (&row)[n], W w) {
+  T s = T(0);
+#pragma unroll
+  for (int nu = 0; nu < n; ++nu) s += row[nu] * w(nu);
+  return s;
+}
+
 // mass-contract ext entries along the first tangential coordinate for the
 // value at (a, b): sum over the cell block of a
 template <typename T>
 __device__ __forceinline__ T ext_mx(const Tab<K, T>* __restrict__ t, const T* arr, int a, int b) {
   const int c0 = (a / n) * n, mu = a % n;
   T row[n];
-  mass_row<T>(mu, row);
-  T s = T(0);
-#pragma unroll
-  for (int nu = 0; nu < n; ++nu) s += row[nu] * arr[c0 + nu + E * b];
-  return s;
+  face_row<T>(mu, row);
+  return face_dot<T>(row, [&](int nu) { return arr[c0 + nu + E * b]; });
 }
 template <typename T>
 __device__ __forceinline__ T ext_my(const Tab<K, T>* __restrict__ t, const T* arr, int a, int b) {
   const int c0 = (b / n) * n, mu = b % n;
   T row[n];
-  mass_row<T>(mu, row);
-  T s = T(0);
-#pragma unroll
-  for (int nu = 0; nu < n; ++nu) s += row[nu] * arr[a + E * (c0 + nu)];
-  return s;
+  face_row<T>(mu, row);
+  return face_dot<T>(row, [&](int nu) { return arr[a + E * (c0 + nu)]; });
 }
 
 // Sides of a y-line (px, pz) (D = 3) or (px) (D = 2): ext_y contracted with M_x.
@@ -725,7 +929,7 @@ __device__ __forceinline__ void yside_load(const T* __restrict__ x, int N, const
   const int cz = (D == 3) ? P.lo[2] + pz / n : 0;
   const int az = (D == 3) ? pz % n : 0;
   const bool bl = (P.lo[1] == 0), br = (P.lo[1] + 1 == N - 1);
-  mass_row<T>(px % n, y.row);
+  face_row<T>(px % n, y.row);
   const T* rl = x + cell_index(N, cx, bl ? P.lo[1] : P.lo[1] - 1, cz) * NC + K * n + az * n * n;
   const T* rr = x + cell_index(N, cx, br ? P.lo[1] + 1 : P.lo[1] + 2, cz) * NC + az * n * n;
 #pragma unroll
@@ -744,16 +948,10 @@ __device__ __forceinline__ Sides<T> yside_finish(const YSideRaw<T>& y, int N, co
   if (MODE == 2) return sd;
   const T half = T(0.5);
   if (!sd.bl) {
-    T s = T(0);
-#pragma unroll
-    for (int nu = 0; nu < n; ++nu) s += y.row[nu] * y.l[nu];
-    sd.bL = -half * s;
+    sd.bL = -half * face_dot<T>(y.row, [&](int nu) { return y.l[nu]; });
   }
   if (!sd.br) {
-    T s = T(0);
-#pragma unroll
-    for (int nu = 0; nu < n; ++nu) s += y.row[nu] * y.r[nu];
-    sd.bR = half * s;
+    sd.bR = half * face_dot<T>(y.row, [&](int nu) { return y.r[nu]; });
   }
   return sd;
 }
@@ -773,20 +971,14 @@ __device__ __forceinline__ Sides<T> yline_sides_global(const Tab<K, T>* __restri
   const int az = (D == 3) ? pz % n : 0;
   const T half = T(0.5);
   T row[n];
-  if (!sd.bl || !sd.br) mass_row<T>(px % n, row);
+  if (!sd.bl || !sd.br) face_row<T>(px % n, row);
   if (!sd.bl) {
     const T* r = x + cell_index(N, cx, P.lo[1] - 1, cz) * NC + K * n + az * n * n;
-    T s = T(0);
-#pragma unroll
-    for (int nu = 0; nu < n; ++nu) s += row[nu] * r[nu];
-    sd.bL = -half * s;
+    sd.bL = -half * face_dot<T>(row, [&](int nu) { return r[nu]; });
   }
   if (!sd.br) {
     const T* r = x + cell_index(N, cx, P.lo[1] + 2, cz) * NC + az * n * n;
-    T s = T(0);
-#pragma unroll
-    for (int nu = 0; nu < n; ++nu) s += row[nu] * r[nu];
-    sd.bR = half * s;
+    sd.bR = half * face_dot<T>(row, [&](int nu) { return r[nu]; });
   }
   return sd;
 }
@@ -806,15 +998,16 @@ __device__ __forceinline__ void extz_mass_x_line(const Tab<K, T>* __restrict__ t
   T v[E];
 #pragma unroll
   for (int p = 0; p < E; ++p) v[p] = a[p];
-  // dense mass rows (face data, contracted the same way wherever it is used)
+  // face rows (face data, contracted the same way wherever it is used)
+  constexpr MassRows<T> rows = make_face_rows<T>();
 #pragma unroll
   for (int c = 0; c < 2; ++c)
 #pragma unroll
     for (int mu = 0; mu < n; ++mu) {
-      T s = T(0);
+      T row[n];
 #pragma unroll
-      for (int nu = 0; nu < n; ++nu) s += T(kRef.M[mu * n + nu]) * v[c * n + nu];
-      a[c * n + mu] = s;
+      for (int nu = 0; nu < n; ++nu) row[nu] = rows.v[mu * n + nu];
+      a[c * n + mu] = face_dot<T>(row, [&](int nu) { return v[c * n + nu]; });
     }
 }
 template <typename T, int NCOMP>
@@ -832,32 +1025,6 @@ __device__ __forceinline__ Sides<T> zline_sides(const Tab<K, T>* __restrict__ t,
   } else {
     if (!sd.bl) sd.bL = ext_my<T>(t, z + 0 * NF, px, py);
     if (!sd.br) sd.bR = ext_my<T>(t, z + 1 * NF, px, py);
-  }
-  return sd;
-}
-
-// zline_sides with NCOMP = 1 and the mass row of py (M[py % n][.]) given
-// (loaded by the caller with its other global loads); same arithmetic.
-template <typename T>
-__device__ __forceinline__ Sides<T> zline_sides_row(const T (&row)[n], const T* ext, int N, const PatchPos& P,
-                                                    int px, int py) {
-  Sides<T> sd;
-  sd.bl = (P.lo[2] == 0);
-  sd.br = (P.lo[2] + 1 == N - 1);
-  sd.aL = sd.bL = sd.aR = sd.bR = T(0);
-  sd.lit = false;
-  const int c0 = (py / n) * n;
-  if (!sd.bl) {
-    T s = T(0);
-#pragma unroll
-    for (int nu = 0; nu < n; ++nu) s += row[nu] * ext[px + E * (c0 + nu)];
-    sd.bL = s;
-  }
-  if (!sd.br) {
-    T s = T(0);
-#pragma unroll
-    for (int nu = 0; nu < n; ++nu) s += row[nu] * ext[NF + px + E * (c0 + nu)];
-    sd.bR = s;
   }
   return sd;
 }
@@ -880,10 +1047,7 @@ constexpr bool kZShfl = (TPP <= 64) && (64 % TPP == 0);
 // held one per lane (wl: the lane's index in its wave)
 template <typename T>
 __device__ __forceinline__ T ycontract_lanes(const T (&row)[n], T v, int wl, int mu) {
-  T s = T(0);
-#pragma unroll
-  for (int nu = 0; nu < n; ++nu) s += row[nu] * __shfl(v, wl + E * (nu - mu), 64);
-  return s;
+  return face_dot<T>(row, [&](int nu) { return __shfl(v, wl + E * (nu - mu), 64); });
 }
 
 // Couplings (alpha, beta) of one face node of a neighbour cell across a y-
@@ -892,47 +1056,18 @@ __device__ __forceinline__ T ycontract_lanes(const T (&row)[n], T v, int wl, int
 template <typename T, int SIDE>
 __device__ __forceinline__ void face_node(T sg, const T (&v)[n], T& al, T& be) {
   const T half = T(0.5);
-  T g = T(0), tr = T(0);
-#pragma unroll
-  for (int j = 0; j < n; ++j) {
-    g += (SIDE == 0 ? T(kRef.d1[j]) : T(kRef.d0[j])) * v[j];
-    if (j == (SIDE == 0 ? K : 0)) tr = v[j];
-  }
-  al = (SIDE == 0) ? (half * g - sg * tr) : (-sg * tr - half * g);
+  const T tr = v[SIDE == 0 ? K : 0];
+  al = face_alpha<T, SIDE>(sg, face_grad<T, SIDE>([&](int j) { return v[j]; }), tr);
   be = (SIDE == 0) ? -half * tr : half * tr;
 }
 
-// Couplings of the n face nodes nu of an x-block of a neighbour cell across
-// a y- or z-face; node nu, normal index j sits at c[nu + j strideN].
-// a = sum_nu row[nu] alpha(nu), b = sum_nu row[nu] beta(nu).
-template <typename T, int SIDE>
-__device__ __forceinline__ void face_pair(const Tab<K, T>* __restrict__ t, const T* __restrict__ c,
-                                          int strideN, const T (&row)[n], T& a, T& b) {
-  const T sg = t->sigma;
-  T al[n], be[n];
-#pragma unroll
-  for (int nu = 0; nu < n; ++nu) {
-    T v[n];
-#pragma unroll
-    for (int j = 0; j < n; ++j) v[j] = c[nu + j * strideN];
-    face_node<T, SIDE>(sg, v, al[nu], be[nu]);
-  }
-  T sa = T(0), sb = T(0);
-#pragma unroll
-  for (int nu = 0; nu < n; ++nu) sa += row[nu] * al[nu];
-#pragma unroll
-  for (int nu = 0; nu < n; ++nu) sb += row[nu] * be[nu];
-  a = sa;
-  b = sb;
-}
-
-// The lanes of an x-block (n consecutive lanes of a row of E) lie in one wave
-// where E divides 64 (3-D Q1, Q3, Q7).
-constexpr bool kXShfl = (64 % E) == 0;
+// The lanes of an x-block (n consecutive lanes of a row of E) are one quad or
+// half of one where n is 4 or 2 (Q1, Q3).
+constexpr bool kFaceDPP = (n == 2 || n == 4);
 
 // sum_nu row[nu] v(lane of node nu in this lane's x-block): the mass
-// contraction of per-node face values held one per lane (wl: the lane's index
-// in its wave, nuo: its node in the block); every lane of the block takes part
+// contraction of per-node face values held one per lane; every lane of the
+// block takes part
 // Node NU of this lane's x-block, read by a DPP quad permutation (x-blocks of
 // 2 or 4 lanes lie in one quad): a VALU move per 32 bits, no LDS crossbar.
 template <int NU>
@@ -951,53 +1086,23 @@ __device__ __forceinline__ float dpp_bcast(float v) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, false));
 }
 template <typename T>
-__device__ __forceinline__ T xcontract_lanes(const T (&row)[n], T v, int wl, int nuo) {
+__device__ __forceinline__ T xcontract_lanes(const T (&row)[n], T v) {
   T s = T(0);
-  if constexpr (n == 2 || n == 4) {
+  if constexpr (kFaceDPP) {
     s += row[0] * dpp_bcast<xblock_dpp<0>()>(v);
     s += row[1] * dpp_bcast<xblock_dpp<1>()>(v);
     if constexpr (n == 4) {
       s += row[2] * dpp_bcast<xblock_dpp<2>()>(v);
       s += row[3] * dpp_bcast<xblock_dpp<3>()>(v);
     }
-  } else {
-#pragma unroll
-    for (int nu = 0; nu < n; ++nu) s += row[nu] * __shfl(v, wl - nuo + nu, 64);
   }
   return s;
 }
 
-// Dirichlet smoothers' z-face traces in registers (patches of one wave):
-// lane (px, py) reads the n traces of its x-block on each z-neighbour and
-// contracts beta = -+t/2 with its mass row (the values gather_ext +
-// extz_mass_x_line leave in LDS) ...
-template <typename T>
-__device__ __forceinline__ void rfz_traces(const T* __restrict__ x, int N, const PatchPos& P, int lane,
-                                           T& wz0, T& wz1) {
-  const int px = lane % E, q = lane / E;
-  T rowx[n];
-  mass_row<T>(px % n, rowx);
-  const T half = T(0.5);
-  const int cx = P.lo[0] + px / n, cy = P.lo[1] + q / n;
-  const long long o = (long long)n * (q % n);
-  wz0 = wz1 = T(0);
-  if (P.lo[2] > 0) {
-    const T* c = x + cell_index(N, cx, cy, P.lo[2] - 1) * NC + o + K * n * n;
-    T s = T(0);
-#pragma unroll
-    for (int nu = 0; nu < n; ++nu) s += rowx[nu] * (-half * c[nu]);
-    wz0 = s;
-  }
-  if (P.lo[2] + 2 < N) {
-    const T* c = x + cell_index(N, cx, cy, P.lo[2] + 2) * NC + o;
-    T s = T(0);
-#pragma unroll
-    for (int nu = 0; nu < n; ++nu) s += rowx[nu] * (half * c[nu]);
-    wz1 = s;
-  }
-}
-// ... and the z-line (px, py = lane / E) contracts them along y across lanes
-// (the values zline_sides forms from LDS); TRACES false: no neighbour data
+// Dirichlet smoothers' z-face traces in registers (patches of one wave): lane
+// (px, py) holds the traces of its x-block on each z-neighbour contracted with
+// its mass row (operator_passes), and the z-line (px, py = lane / E) contracts
+// them along y across lanes. TRACES false: no neighbour data
 template <typename T, bool TRACES>
 __device__ __forceinline__ Sides<T> rfz_sides(int N, const PatchPos& P, int lane, T wz0, T wz1) {
   Sides<T> sd;
@@ -1008,7 +1113,7 @@ __device__ __forceinline__ Sides<T> rfz_sides(int N, const PatchPos& P, int lane
   if constexpr (TRACES) {
     const int py = lane / E;
     T rowy[n];
-    mass_row<T>(py % n, rowy);
+    face_row<T>(py % n, rowy);
     const int wl = threadIdx.x & 63;
     const T zL = ycontract_lanes<T>(rowy, wz0, wl, py % n);
     const T zR = ycontract_lanes<T>(rowy, wz1, wl, py % n);
@@ -1088,18 +1193,10 @@ __device__ __forceinline__ void operator_passes(const Tab<K, T>* __restrict__ t,
         zl[nu] = cl[nu];
         zr[nu] = cr[nu];
       }
-      mass_row<T>(q % n, rowz);
+      face_row<T>(q % n, rowz);
     }
-    // patches of several waves (no register z-faces): this lane's z-face node
-    // (px, q) on both z-neighbours, the traces gather_ext would read
-    T ztr0 = T(0), ztr1 = T(0);
-    if constexpr (D == 3 && !RFZ && MODE == 1) {
-      static_assert(NF == TPP, "one z-face node per lane");
-      const int cx = P.lo[0] + px / n, cy = P.lo[1] + q / n;
-      const long long o = px % n + (long long)n * (q % n);
-      ztr0 = x[cell_index(N, cx, cy, P.lo[2] > 0 ? P.lo[2] - 1 : P.lo[2]) * NC + o + K * n * n];
-      ztr1 = x[cell_index(N, cx, cy, P.lo[2] + 2 < N ? P.lo[2] + 2 : P.lo[2]) * NC + o];
-    }
+    // (patches of several waves take the z-face traces in the direct form only)
+    static_assert(D == 2 || RFZ || MODE != 1, "operator passes with z-traces: one-wave patches");
     const int py = lane % E, pz = lane / E;
     const long long row0 = xrow_offset(N, P, py, pz);
     read_xline<T>(x, row0, xl);
@@ -1125,10 +1222,8 @@ __device__ __forceinline__ void operator_passes(const Tab<K, T>* __restrict__ t,
         wz1 = s;
       }
     } else if constexpr (!RFZ && D == 3) {
-      // the z-face traces as gather_ext stores them (zeros for MODE 2)
-      const T half = T(0.5);
-      ext[lane] = (MODE == 1 && P.lo[2] > 0) ? -half * ztr0 : T(0);
-      ext[NF + lane] = (MODE == 1 && P.lo[2] + 2 < N) ? half * ztr1 : T(0);
+      ext[lane] = T(0);  // MODE 2: no z-face traces
+      ext[NF + lane] = T(0);
     }
     Sides<T> sd;
     sd.bl = xbl;
@@ -1147,7 +1242,7 @@ __device__ __forceinline__ void operator_passes(const Tab<K, T>* __restrict__ t,
     store_line(A, base, stride, a);
     store_line(B, base, stride, b);
   } else if (RFA && active) {
-    static_assert(!RFA || kXShfl, "x-blocks within a wave");
+      static_assert(!RFA || kFaceDPP, "x-blocks within a quad");
     // register face data (operator, patches of one wave): every global load
     // first, as in k_apply_rf -- this lane's node column of each neighbour
     // face block, the x-line and its x-neighbours' rows -- then the per-node
@@ -1195,8 +1290,8 @@ __device__ __forceinline__ void operator_passes(const Tab<K, T>* __restrict__ t,
       }
     }
     T rowx[n];
-    mass_row<T>(nuo, rowx);
-    mass_row<T>(q % n, rowz);
+    face_row<T>(nuo, rowx);
+    face_row<T>(q % n, rowz);
     const T sg = t->sigma;
     T nya0, nyb0, nya1, nyb1, nza0, nzb0, nza1, nzb1;
     face_node<T, 0>(sg, fy0, nya0, nyb0);
@@ -1211,32 +1306,16 @@ __device__ __forceinline__ void operator_passes(const Tab<K, T>* __restrict__ t,
     line_sipg<T, false>(t, xl, sd, b, n0x, nEx);
     store_line(A, base, stride, a);
     store_line(B, base, stride, b);
-    const T sya0 = xcontract_lanes<T>(rowx, nya0, wl, nuo), syb0 = xcontract_lanes<T>(rowx, nyb0, wl, nuo);
-    const T sya1 = xcontract_lanes<T>(rowx, nya1, wl, nuo), syb1 = xcontract_lanes<T>(rowx, nyb1, wl, nuo);
-    const T sza0 = xcontract_lanes<T>(rowx, nza0, wl, nuo), szb0 = xcontract_lanes<T>(rowx, nzb0, wl, nuo);
-    const T sza1 = xcontract_lanes<T>(rowx, nza1, wl, nuo), szb1 = xcontract_lanes<T>(rowx, nzb1, wl, nuo);
+    const T sya0 = xcontract_lanes<T>(rowx, nya0), syb0 = xcontract_lanes<T>(rowx, nyb0);
+    const T sya1 = xcontract_lanes<T>(rowx, nya1), syb1 = xcontract_lanes<T>(rowx, nyb1);
+    const T sza0 = xcontract_lanes<T>(rowx, nza0), szb0 = xcontract_lanes<T>(rowx, nzb0);
+    const T sza1 = xcontract_lanes<T>(rowx, nza1), szb1 = xcontract_lanes<T>(rowx, nzb1);
     if (!ybl) { ya0 = sya0; yb0 = syb0; }
     if (!ybr) { ya1 = sya1; yb1 = syb1; }
     if (!zbl) { za0 = sza0; zb0 = szb0; }
     if (!zbr) { za1 = sza1; zb1 = szb1; }
   } else if (active) {
-    if constexpr (MODE != 0) ysd_global = yline_sides_global<T, MODE>(t, x, N, P, lane % E, lane / E);
-    if constexpr (RFZ) {
-      if constexpr (MODE == 1) rfz_traces<T>(x, N, P, lane, wz0, wz1);
-    } else if constexpr (RFA) {
-      const int px = lane % E, q = lane / E;
-      T rowx[n];
-      mass_row<T>(px % n, rowx);
-      const int cx = P.lo[0] + px / n;
-      const long long oy = (long long)(n * n) * (q % n), oz = (long long)n * (q % n);
-      const int cz = P.lo[2] + q / n, cy = P.lo[1] + q / n;
-      if (P.lo[1] > 0) face_pair<T, 0>(t, x + cell_index(N, cx, P.lo[1] - 1, cz) * NC + oy, n, rowx, ya0, yb0);
-      if (P.lo[1] + 2 < N) face_pair<T, 1>(t, x + cell_index(N, cx, P.lo[1] + 2, cz) * NC + oy, n, rowx, ya1, yb1);
-      if (P.lo[2] > 0) face_pair<T, 0>(t, x + cell_index(N, cx, cy, P.lo[2] - 1) * NC + oz, n * n, rowx, za0, zb0);
-      if (P.lo[2] + 2 < N) face_pair<T, 1>(t, x + cell_index(N, cx, cy, P.lo[2] + 2) * NC + oz, n * n, rowx, za1, zb1);
-    } else {
-      gather_ext<T, MODE>(t, x, N, P, lane, ext);
-    }
+    gather_ext<T, MODE>(t, x, N, P, lane, ext);
     for (int i = lane; i < NL; i += TPP) {
       const int py = i % E, pz = i / E;
       const long long row0 = xrow_offset(N, P, py, pz);
@@ -1457,8 +1536,8 @@ __device__ __forceinline__ void apply_rf_body(const Tab<K, T>* t, const PatchGri
   // lane = px + E q: y-line (px, pz = q), z-face node (px, py = q)
   const int px = lane % E, q = lane / E;
   T rowx[n], rowy[n];
-  mass_row<T>(px % n, rowx);
-  mass_row<T>(q % n, rowy);
+  face_row<T>(px % n, rowx);
+  face_row<T>(q % n, rowy);
   const bool ybl = (P.lo[1] == 0), ybr = (P.lo[1] + 1 == N - 1);
   const bool zbl = (P.lo[2] == 0), zbr = (P.lo[2] + 1 == N - 1);
   T ya0 = T(0), yb0 = T(0), ya1 = T(0), yb1 = T(0);
@@ -1467,33 +1546,8 @@ __device__ __forceinline__ void apply_rf_body(const Tab<K, T>* t, const PatchGri
   T nya0 = T(0), nyb0 = T(0), nya1 = T(0), nyb1 = T(0);
   T nza0 = T(0), nzb0 = T(0), nza1 = T(0), nzb1 = T(0);
   const int nuo = px % n;
-  if (!kXShfl && active) {
-    // x-blocks straddle waves: each lane reads whole face blocks
-    const int cx = P.lo[0] + px / n;
-    {
-      const int cz = P.lo[2] + q / n;
-      const long long o = (long long)(n * n) * (q % n);
-      if (!ybl) face_pair<T, 0>(t, xr + cell_index(N, cx, P.lo[1] - 1, cz) * NC + o, n, rowx, ya0, yb0);
-      if (!ybr) face_pair<T, 1>(t, xr + cell_index(N, cx, P.lo[1] + 2, cz) * NC + o, n, rowx, ya1, yb1);
-    }
-    {
-      const int cy = P.lo[1] + q / n;
-      const long long o = (long long)n * (q % n);
-      if (!zbl) face_pair<T, 0>(t, xr + cell_index(N, cx, cy, P.lo[2] - 1) * NC + o, n * n, rowx, za0, zb0);
-      if (!zbr) face_pair<T, 1>(t, xr + cell_index(N, cx, cy, P.lo[2] + 2) * NC + o, n * n, rowx, za1, zb1);
-    }
-    const int py = lane % E, pz = lane / E;
-    const long long row0 = xrow_offset(N, P, py, pz);
-    read_xline<T>(xr, row0, xl);
-    const Sides<T> sd = xline_sides<T, 0>(t, xr, N, P, row0);
-    int base, stride;
-    line_geom(0, lane, base, stride);
-    Line<T> a, b;
-    line_mass<T>(t, xl, a);
-    line_sipg<T, false>(t, xl, sd, b);
-    store_line(A, base, stride, a);
-    store_line(B, base, stride, b);
-  } else if (kXShfl && active) {
+  Sides<T> xsd{};
+  if (active) {
     // Every global load first (one memory round trip): this lane's node
     // column of each neighbour face block (n values along the normal), the
     // x-line and the rows of its x-neighbours; missing neighbours read the
@@ -1541,27 +1595,45 @@ __device__ __forceinline__ void apply_rf_body(const Tab<K, T>* t, const PatchGri
     face_node<T, 1>(sg, fy1, nya1, nyb1);
     face_node<T, 0>(sg, fz0, nza0, nzb0);
     face_node<T, 1>(sg, fz1, nza1, nzb1);
+    xsd = xsides_rows<T>(sg, xbl, xbr, rl, rr);
+    if constexpr (!kFaceDPP) {
+      // node couplings to LDS, in the space the tiles take afterwards
+      const T nv[8] = {nya0, nyb0, nya1, nyb1, nza0, nzb0, nza1, nzb1};
+#pragma unroll
+      for (int f = 0; f < 8; ++f) A[f * NF + lane] = nv[f];
+    }
+  }
+  // face couplings contracted with M_x over the nodes of each x-block: across
+  // lanes by DPP where a block is a quad or less (Q1, Q3), else from LDS.  (All
+  // lanes of a patch take part.)
+  T fc[8];
+  if constexpr (kFaceDPP) {
+    fc[0] = xcontract_lanes<T>(rowx, nya0), fc[1] = xcontract_lanes<T>(rowx, nyb0);
+    fc[2] = xcontract_lanes<T>(rowx, nya1), fc[3] = xcontract_lanes<T>(rowx, nyb1);
+    fc[4] = xcontract_lanes<T>(rowx, nza0), fc[5] = xcontract_lanes<T>(rowx, nzb0);
+    fc[6] = xcontract_lanes<T>(rowx, nza1), fc[7] = xcontract_lanes<T>(rowx, nzb1);
+  } else {
+    __syncthreads();
+    if (active) {
+      const T* w = A + lane - nuo;
+#pragma unroll
+      for (int f = 0; f < 8; ++f) fc[f] = face_dot<T>(rowx, [&](int nu) { return w[f * NF + nu]; });
+    }
+    __syncthreads();
+  }
+  if (active) {
+    if (!ybl) { ya0 = fc[0]; yb0 = fc[1]; }
+    if (!ybr) { ya1 = fc[2]; yb1 = fc[3]; }
+    if (!zbl) { za0 = fc[4]; zb0 = fc[5]; }
+    if (!zbr) { za1 = fc[6]; zb1 = fc[7]; }
     // X0: a = M_x x -> A, b = L_x x -> B
-    const Sides<T> sd = xsides_rows<T>(sg, xbl, xbr, rl, rr);
     int base, stride;
     line_geom(0, lane, base, stride);
     Line<T> a, b;
     line_mass<T>(t, xl, a);
-    line_sipg<T, false>(t, xl, sd, b);
+    line_sipg<T, false>(t, xl, xsd, b);
     store_line(A, base, stride, a);
     store_line(B, base, stride, b);
-  }
-  // face couplings contracted with M_x across the lanes of each x-block
-  // (all lanes of a patch take part)
-  if constexpr (kXShfl) {
-    const T sya0 = xcontract_lanes<T>(rowx, nya0, wl, nuo), syb0 = xcontract_lanes<T>(rowx, nyb0, wl, nuo);
-    const T sya1 = xcontract_lanes<T>(rowx, nya1, wl, nuo), syb1 = xcontract_lanes<T>(rowx, nyb1, wl, nuo);
-    const T sza0 = xcontract_lanes<T>(rowx, nza0, wl, nuo), szb0 = xcontract_lanes<T>(rowx, nzb0, wl, nuo);
-    const T sza1 = xcontract_lanes<T>(rowx, nza1, wl, nuo), szb1 = xcontract_lanes<T>(rowx, nzb1, wl, nuo);
-    if (!ybl) { ya0 = sya0; yb0 = syb0; }
-    if (!ybr) { ya1 = sya1; yb1 = syb1; }
-    if (!zbl) { za0 = sza0; zb0 = szb0; }
-    if (!zbr) { za1 = sza1; zb1 = szb1; }
   }
   if constexpr (!kZShfl) {  // x-contracted z-face values for the y-contraction
     if (active) {
@@ -1608,14 +1680,11 @@ __device__ __forceinline__ void apply_rf_body(const Tab<K, T>* t, const PatchGri
     if (active) {
       const T* wz = B + TS;
       const int f0 = px + E * (q - muy);
-#pragma unroll
-      for (int nu = 0; nu < n; ++nu) zaL += rowy[nu] * wz[0 * NF + f0 + E * nu];
-#pragma unroll
-      for (int nu = 0; nu < n; ++nu) zbL += rowy[nu] * wz[1 * NF + f0 + E * nu];
-#pragma unroll
-      for (int nu = 0; nu < n; ++nu) zaR += rowy[nu] * wz[2 * NF + f0 + E * nu];
-#pragma unroll
-      for (int nu = 0; nu < n; ++nu) zbR += rowy[nu] * wz[3 * NF + f0 + E * nu];
+      auto zrow = [&](int f) { return face_dot<T>(rowy, [&](int nu) { return wz[f * NF + f0 + E * nu]; }); };
+      zaL = zrow(0);
+      zbL = zrow(1);
+      zaR = zrow(2);
+      zbR = zrow(3);
     }
   }
   // Z: y = M_z c + L_z d
@@ -1764,22 +1833,568 @@ k_mass(const Tab<K, T>* __restrict__ t, PatchGrid g, T scale, const T* __restric
 // Q3) through operator_passes (two tiles of LDS per patch), otherwise through
 // the apply's register-face body (two tiles and four z-face rows); no face
 // arrays either way.
-constexpr bool kFullRF = (D == 3) && kZShfl && kXShfl;
+constexpr bool kFullRF = (D == 3) && kZShfl;
 constexpr bool kFullOnApplyRF = kApplyRF && !kFullRF;
+// The Dirichlet smoothers (MODE 1, 2) take the direct form (gs_body) where
+// direct_smoother says so.
+template <int MODE>
+constexpr bool kDirect = (MODE == 1 || MODE == 2) && direct_smoother(D, K);
+
+// LDS of the direct form per patch: the tile, whose space first holds the face
+// fields -- in 3-D 16 planes of E x E values with the tile's row and plane
+// strides (so that lines along either direction of a plane are read without
+// bank conflicts), in 2-D 8 rows of E.
+// In 3-D the mass matrix follows where n > 4.
+constexpr int kGsM = (16 > E ? 16 : E) * SZ;
+constexpr int kGsPP = (D == 3) ? kGsM + (n > 4 ? n * n : 0) : (TS > 8 * E ? TS : 8 * E);
 template <int MODE>
 __host__ __device__ constexpr int smooth_pp() {
-  return MODE == 3 ? (kFullRF ? 2 * TS : kFullOnApplyRF ? kApplyRFPP : Smem<2, (D - 1) * 2 * 2 * NF>::per_patch)
+  return kDirect<MODE> ? kGsPP
+         : MODE == 3 ? (kFullRF ? 2 * TS : kFullOnApplyRF ? kApplyRFPP : Smem<2, (D - 1) * 2 * 2 * NF>::per_patch)
                    : Smem<2, (D - 2) * 2 * NF>::per_patch;
+}
+
+// ------------------------------------- Dirichlet smoothers, direct form
+// A Dirichlet patch's update x_V + A_VV^{-1} (b - A x)_V does not depend on the
+// old values on V: it is the solution of A_VV x_V = b_V - A_VR x_R, with x_R
+// the values the patch does not update (its dropped end nodes and the traces
+// of the cells beyond them).  So no operator pass runs over the tile: with the
+// 1-D relation (HostTables) S^T L v = Lambda S^T M v + gp v_c + gt u (v_c the
+// dropped end values of a line, u the outer traces),
+//   S3 x_V = Lambda^{-1} [S3^T b - sum_dir (gp (x) c_dir + gt (x) t_dir)] - w,
+// where c_dir, t_dir are the dropped end layer and the outer trace of the two
+// patch faces of direction dir, transformed by S^T M along the face, and w is
+// S3^T M3 of the dropped nodes.  The forward passes S_z^T, S_y^T, S_x^T run over
+// z-, y-, x-lines and each adds the faces of its own direction, where they are
+// scalars of the lane: the masses alone act on a face along the directions
+// whose S^T pass still follows.  On the way back w is taken off face by face
+// (x-faces in the eigenbasis along y and z, y-faces in it along z, z-faces as
+// plain nodal values), so that every dropped node counts once.
+//
+// What bounds it: the volume passes are six contractions of E-point lines
+// instead of thirteen, five phases and one tile of LDS instead of seven and
+// two; the faces cost O(E^2) lines per patch.
+
+// Lines whose registers (E values, several lines live at once) leave no room for
+// loads issued ahead: there the loads stay with their use.
+template <typename T>
+constexpr bool kGsTight = (D == 3) && E >= 10;
+
+// Value of a patch face pair at one point: sum and difference of the left and
+// right layer; an end that is not dropped counts as zero (type 0 uses both
+// parts, types 1 and 2 the sum alone).
+template <typename T>
+struct FacePair {
+  T s, d;
+};
+template <typename T>
+__device__ __forceinline__ FacePair<T> face_sum(int ty, T l, T r) {
+  return FacePair<T>{((ty & 1) ? T(0) : l) + ((ty & 2) ? T(0) : r), l - r};
+}
+
+// o = S^T v - gp F - gt U, the ends and traces of the line as face pairs
+template <typename T, int TY, bool OPQ>
+__device__ __forceinline__ void line_fwd_t(const Tab<K, T>* __restrict__ t, const Line<T>& v, const FacePair<T>& F,
+                                           const FacePair<T>& U, Line<T>& o) {
+  using B = FDB<SP_DIR, TY>;
+  const Coef<T> S = pass_coef<T, OPQ>(t->S[TY]), gp = pass_coef<T, OPQ>(t->gp[TY]),
+                gt = pass_coef<T, OPQ>(t->gt[TY]);
+  T vp[kEOH], vm[kEOH];
+  if constexpr (kEO && TY == 0) eo_split<T>(v, vp, vm);
+#pragma unroll
+  for (int q = 0; q < E; ++q) {
+    if (q >= B::QN) {
+      o.v[q] = T(0);
+      continue;
+    }
+    const bool odd = TY == 0 && q >= kEOH;
+    T s = -gp[q] * (odd ? F.d : F.s);
+    s -= gt[q] * (odd ? U.d : U.s);
+    if constexpr (kEO && TY == 0) {
+#pragma unroll
+      for (int k = 0; k < kEOH; ++k) s += S[(1 + k) * E + q] * (odd ? vm[k] : vp[k]);
+    } else {
+#pragma unroll
+      for (int p = B::PLO; p < B::PHI; ++p) s += S[p * E + q] * v.v[p];
+    }
+    o.v[q] = s;
+  }
+}
+// o = S (v - gm W), W the dropped end nodes of the line
+template <typename T, int TY, bool OPQ>
+__device__ __forceinline__ void line_back_t(const Tab<K, T>* __restrict__ t, Line<T>& v, const FacePair<T>& W,
+                                            Line<T>& o) {
+  using B = FDB<SP_DIR, TY>;
+  const Coef<T> gm = pass_coef<T, OPQ>(t->gm[TY]);
+#pragma unroll
+  for (int q = 0; q < B::QN; ++q) v.v[q] -= gm[q] * ((TY == 0 && q >= kEOH) ? W.d : W.s);
+  const Coef<T> S = pass_coef<T, OPQ>(t->S[TY]);
+  if constexpr (kEO && TY == 0) {
+    // written in node order, as the other types write theirs: the compiler
+    // then merges the branches' stores into one line without a
+    // runtime-indexed copy of it (which would live in scratch)
+    T e[kEOH], d[kEOH];
+#pragma unroll
+    for (int k = 0; k < kEOH; ++k) {
+      e[k] = d[k] = T(0);
+#pragma unroll
+      for (int q = 0; q < kEOH; ++q) e[k] += S[(1 + k) * E + q] * v.v[q];
+#pragma unroll
+      for (int q = 0; q < kEOH; ++q) d[k] += S[(1 + k) * E + kEOH + q] * v.v[kEOH + q];
+    }
+    o.v[0] = T(0);
+#pragma unroll
+    for (int k = 0; k < kEOH; ++k) o.v[1 + k] = e[k] + d[k];
+#pragma unroll
+    for (int k = kEOH - 1; k >= 0; --k) o.v[E - 2 - k] = e[k] - d[k];
+    o.v[E - 1] = T(0);
+    return;
+  }
+#pragma unroll
+  for (int p = 0; p < E; ++p) {
+    T s = T(0);
+    if (p >= B::PLO && p < B::PHI) {
+#pragma unroll
+      for (int q = 0; q < B::QN; ++q) s += S[p * E + q] * v.v[q];
+    }
+    o.v[p] = s;
+  }
+}
+// the x-pass: forward, 1 / (sum lambda), the x-faces' part of w, back
+template <typename T, int TY, bool OPQ>
+__device__ __forceinline__ void line_turn_t(const Tab<K, T>* __restrict__ t, const Line<T>& v, const FacePair<T>& F,
+                                            const FacePair<T>& U, const FacePair<T>& W, T inv_scale,
+                                            const T* rs, Line<T>& o) {
+  constexpr int QN = FDB<SP_DIR, TY>::QN;
+  Line<T> w;
+  T r[QN];
+  if constexpr (!kGsTight<T>) {
+#pragma unroll
+    for (int q = 0; q < QN; ++q) r[q] = rs[q * NL];
+  }
+  line_fwd_t<T, TY, OPQ>(t, v, F, U, w);
+  if constexpr (kGsTight<T>) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < QN; ++q) r[q] = rs[q * NL];
+  }
+#pragma unroll
+  for (int q = 0; q < QN; ++q) w.v[q] = w.v[q] * (inv_scale * r[q]);
+  line_back_t<T, TY, OPQ>(t, w, W, o);
+}
+// o = S^T M v over the whole line
+template <typename T, int TY>
+__device__ __forceinline__ void line_MS_t(const Tab<K, T>* __restrict__ t, const Line<T>& v, Line<T>& o) {
+  const Coef<T> S = pass_coef<T, true>(t->MS[TY]);
+  T vp[n], vm[n];
+  if constexpr (TY == 0) {  // even and odd eigenvectors: half columns on sums and differences
+#pragma unroll
+    for (int p = 0; p < n; ++p) {
+      vp[p] = v.v[p] + v.v[E - 1 - p];
+      vm[p] = v.v[p] - v.v[E - 1 - p];
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < E; ++q) {
+    T s = T(0);
+    if (q < FDB<SP_DIR, TY>::QN) {
+      if constexpr (TY == 0) {
+#pragma unroll
+        for (int p = 0; p < n; ++p) s += S[p * E + q] * (q < kEOH ? vp[p] : vm[p]);
+      } else {
+#pragma unroll
+        for (int p = 0; p < E; ++p) s += S[p * E + q] * v.v[p];
+      }
+    }
+    o.v[q] = s;
+  }
+}
+
+// The passes for a patch type known at compile time (INT: an interior patch,
+// type 0 in every direction) or not.  Type 3, both ends on the boundary, does
+// not occur: the smoothers run on meshes of at least four cells a direction.
+template <typename T, bool INT>
+struct GsLine {
+  // an interior patch's passes share S and the couplings where these fit in
+  // the scalar registers
+  static constexpr bool OPQ = !INT || (2 * kEOH * ((kEO ? kEOH : 2 * kEOH) + 3)) * (int)sizeof(T) > 4 * 72;
+  static __device__ __forceinline__ void fwd(const Tab<K, T>* __restrict__ t, int ty, const Line<T>& v,
+                                             const FacePair<T>& F, const FacePair<T>& U, Line<T>& o) {
+    if constexpr (INT) return line_fwd_t<T, 0, OPQ>(t, v, F, U, o);
+    switch (ty) {
+      case 0: line_fwd_t<T, 0, OPQ>(t, v, F, U, o); break;
+      case 1: line_fwd_t<T, 1, OPQ>(t, v, F, U, o); break;
+      default: line_fwd_t<T, 2, OPQ>(t, v, F, U, o); break;
+    }
+  }
+  static __device__ __forceinline__ void back(const Tab<K, T>* __restrict__ t, int ty, Line<T>& v,
+                                              const FacePair<T>& W, Line<T>& o) {
+    if constexpr (INT) return line_back_t<T, 0, OPQ>(t, v, W, o);
+    switch (ty) {
+      case 0: line_back_t<T, 0, OPQ>(t, v, W, o); break;
+      case 1: line_back_t<T, 1, OPQ>(t, v, W, o); break;
+      default: line_back_t<T, 2, OPQ>(t, v, W, o); break;
+    }
+  }
+  static __device__ __forceinline__ void turn(const Tab<K, T>* __restrict__ t, int ty, const Line<T>& v,
+                                              const FacePair<T>& F, const FacePair<T>& U, const FacePair<T>& W,
+                                              T inv_scale, const T* rs, Line<T>& o) {
+    if constexpr (INT) return line_turn_t<T, 0, OPQ>(t, v, F, U, W, inv_scale, rs, o);
+    switch (ty) {
+      case 0: line_turn_t<T, 0, OPQ>(t, v, F, U, W, inv_scale, rs, o); break;
+      case 1: line_turn_t<T, 1, OPQ>(t, v, F, U, W, inv_scale, rs, o); break;
+      default: line_turn_t<T, 2, OPQ>(t, v, F, U, W, inv_scale, rs, o); break;
+    }
+  }
+  static __device__ __forceinline__ void ms(const Tab<K, T>* __restrict__ t, int ty, const Line<T>& v, Line<T>& o) {
+    if constexpr (INT) return line_MS_t<T, 0>(t, v, o);
+    switch (ty) {
+      case 0: line_MS_t<T, 0>(t, v, o); break;
+      case 1: line_MS_t<T, 1>(t, v, o); break;
+      default: line_MS_t<T, 2>(t, v, o); break;
+    }
+  }
+};
+
+// The scalar cache starts every launch empty, and a pass that reads its
+// coefficients where it needs them waits for the L2 each time.  warm_coef reads
+// one word of every cache line of [p, p + count) at the start, together with
+// the first vector loads; the caller hands the combined words to warm_wait,
+// behind those loads.
+template <typename T>
+__device__ __forceinline__ unsigned warm_coef(const T* p, int count) {
+  const Coef<unsigned> w = (Coef<unsigned>)(unsigned long long)p;
+  unsigned x = 0;
+#pragma unroll
+  for (int i = 0; i < count * (int)sizeof(T) / 4; i += 16) x ^= w[i];
+  return x;
+}
+__device__ __forceinline__ void warm_wait(unsigned x) { asm volatile("" ::"s"(x)); }
+
+// i / DIV for the small non-negative indices of a patch (24-bit multiply and
+// shift; exact below 512 for the divisors 2..64)
+template <int DIV>
+__device__ __forceinline__ int small_div(int i) {
+  static_assert(DIV >= 2 && DIV <= 64, "checked divisors");
+  if constexpr ((DIV & (DIV - 1)) == 0) return (unsigned)i / DIV;
+  return (int)(__umul24((unsigned)i, 65536u / DIV + 1) >> 16);
+}
+
+// Element o of a vector part that starts at the (wave-uniform) address p:
+// 32-bit offsets, so that the loads take the scalar base and one lane offset.
+// The offsets span at most three planes of cells (3 N^(D-1) (k+1)^D entries),
+// below 4 GB for every vector that fits the device.
+template <typename T>
+__device__ __forceinline__ const T& at32(const T* p, unsigned o) {
+  return *(const T*)((const char*)p + (size_t)(o * (unsigned)sizeof(T)));
+}
+template <typename T>
+__device__ __forceinline__ T& at32(T* p, unsigned o) {
+  return *(T*)((char*)p + (size_t)(o * (unsigned)sizeof(T)));
+}
+
+// One patch of one colour (see smooth_body for the arguments).  MODE 2 (the
+// paper's residual) differs only in the outer trace, for which it takes the
+// patch's own end value.  ZERO: x = 0 on entry, so there are no faces, and
+// every node of the tile is written.  INT: the patch is an interior one.
+//
+// Order of the loads: the face layers and lines, then (where the registers
+// allow it) b, all before the first of them is used -- one memory round trip.
+template <typename T, int MODE, bool ZERO, bool INT>
+__device__ __forceinline__ void gs_body(const Tab<K, T>* __restrict__ t, int N, const PatchPos& P, T scale,
+                                        T inv_scale, T* __restrict__ xr, const T* __restrict__ br, bool active,
+                                        int lane, T* A) {
+  static_assert(NL == TPP && NF == TPP, "one line and one face node per lane");
+  using L1 = GsLine<T, INT>;
+  const int tyx = INT ? 0 : P.ty[0], tyy = INT ? 0 : P.ty[1], tyl = INT ? 0 : P.ty[D - 1];
+  // The lane's coordinates (a, q): in 3-D the lanes run through the plane cell
+  // by cell (cell and node an, am of a; qn, qm of q), as the vectors do, so that
+  // the loads and stores of a plane touch the fewest cache lines: the cache
+  // accesses of the row-by-row order (1030 a wave for 3-D Q4 in FP32) were
+  // what bound the launch there.
+  int an, am, qn = 0, qm = 0;
+  if constexpr (D == 3) {
+    const int cell = small_div<n * n>(lane), in = lane - cell * (n * n);
+    qm = small_div<n>(in);
+    am = in - qm * n;
+    an = cell & 1;
+    qn = cell >> 1;
+  } else {
+    an = small_div<n>(lane);
+    am = lane - an * n;
+  }
+  const int a = an * n + am, q = qn * n + qm;
+  // the lane's line along the last direction: node p of cell c at
+  // x0 + c lc + lo + (p % n) ln
+  constexpr int ln = (D == 3) ? n * n : n;
+  const unsigned cy = (unsigned)N * NC;                       // next cell in y
+  const unsigned lc = (D == 3) ? (unsigned)N * cy : cy;       // next cell in the last direction
+  const long long p0 = cell_index(N, P.lo[0], P.lo[1], D == 3 ? P.lo[2] : 0) * NC;
+  T* x0 = xr + p0;
+  T* x1 = x0 + lc;
+  const T *b0 = br + p0, *b1 = b0 + lc;
+  const unsigned lo = (unsigned)(an * NC + am) + (D == 3 ? (unsigned)qn * cy + (unsigned)(n * qm) : 0u);
+  Line<T> bl;
+  auto load_b = [&]() {
+#pragma unroll
+    for (int p = 0; p < E; ++p) bl.v[p] = at32(p < n ? b0 : b1, lo + (p % n) * ln);
+  };
+  // faces of the last direction (Fl, Ul; Wl nodal) and of the x-direction (F is
+  // scale W), and in 3-D of the y-direction (Wy in the eigenbasis along z)
+  FacePair<T> Fl{}, Ul{}, Wl{}, Ux{}, Wx{}, Fy{}, Uy{}, Wy{};
+  constexpr bool TIGHT = kGsTight<T>;
+  // mass rows of the lane's nodes in x and (3-D) y: short ones by the first
+  // loads, long ones (registers, cache accesses) from LDS at their use
+  constexpr bool ROWLDS = D == 3 && n > 4;
+  // (where the types are known to be uniform and the tables short; an interior
+  // patch reads too little for it to show)
+  constexpr bool WARM = !INT && TPP % 64 == 0 && E * E * (int)sizeof(T) <= 512;
+  unsigned warm = 0;
+  if constexpr (WARM) {
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+      const int ty = i == 0 ? tyx : i == 1 ? tyy : tyl;
+      warm ^= warm_coef<T>(t->S[ty], E * E) ^ warm_coef<T>(t->gp[ty], E) ^ warm_coef<T>(t->gt[ty], E) ^
+              warm_coef<T>(t->gm[ty], E);
+      if (!ZERO && D == 3 && i > 0) warm ^= warm_coef<T>(t->MS[ty], E * E);
+    }
+  }
+  if constexpr (!ZERO) {
+    T rowx[n], rowy[n];
+    if constexpr (!ROWLDS) mass_row<T>(am, rowx);
+    if constexpr (!ROWLDS && D == 3) mass_row<T>(qm, rowy);
+    // raw layers of the last direction at this lane's node: left end, left
+    // trace, right end, right trace (a side on the domain boundary reads the
+    // patch's own node; its value is not used)
+    const bool ownl = MODE == 2 || (tyl & 1), ownr = MODE == 2 || (tyl & 2);
+    T raw[4] = {T(0), T(0), T(0), T(0)};
+    if (active) {
+      raw[0] = at32(x0, lo);
+      raw[1] = ownl ? raw[0] : at32(x0 - lc, lo + K * ln);
+      raw[2] = at32(x1, lo + K * ln);
+      raw[3] = ownr ? raw[2] : at32(x1 + lc, lo);
+    }
+    if constexpr (D == 3) {
+      // lines along z of the y-faces (field f = 0..3: left end, left trace,
+      // right end, right trace; i = px) and x-faces (f = 4..7; i = py):
+      // S_z^T M_z into planes f; the raw z-layers into planes 8..11
+      if (active) {
+        const T* xm = x0 - cy - NC;
+        if (ROWLDS && lane < n * n) A[kGsM + lane] = kMassRows<T>.v[lane];
+#pragma unroll
+        for (int li0 = 0; li0 < 8 * E; li0 += TPP) {
+          const int li = li0 + lane;
+          if (8 * E % TPP != 0 && li >= 8 * E) {
+            if (!TIGHT && li0 == 0) load_b();
+            break;
+          }
+          const int f = small_div<E>(li), i = li - f * E;
+          const int in = small_div<n>(i), im = i - in * n;
+          const bool xdir = f >= 4, right = (f & 2) != 0;
+          const bool trace = (f & 1) && MODE != 2 && !((xdir ? tyx : tyy) & (right ? 2 : 1));
+          // the layer's cell along the face normal (lo is 1: xm lies one cell
+          // below) and its node there; i runs over the tangential direction
+          const unsigned cn = (right ? 2u : 1u) + (trace ? (right ? 1u : ~0u) : 0u);
+          const unsigned kn = (right != trace) ? K : 0;
+          const unsigned o = xdir ? cn * NC + kn + (unsigned)(in + 1) * cy + n * im
+                                  : cn * cy + n * kn + (unsigned)((in + 1) * NC + im);
+          Line<T> v, w;
+#pragma unroll
+          for (int p = 0; p < E; ++p) v.v[p] = at32(p < n ? xm : xm + lc, o + (p % n) * ln);
+          if (!TIGHT && li0 == 0) load_b();
+          if (WARM && li0 == 0) warm_wait(warm);
+          L1::ms(t, tyl, v, w);
+#pragma unroll
+          for (int p = 0; p < E; ++p) A[f * SZ + p * SY + i] = w.v[p];
+        }
+#pragma unroll
+        for (int f = 0; f < 4; ++f) A[(8 + f) * SZ + q * SY + a] = raw[f];
+      }
+      __syncthreads();
+      // M_x on the z-layers (planes 8..11 -> 12..15) and on the y-faces (this
+      // lane: px = a, z-coefficient q), S_y^T M_y on the x-faces' lines
+      if (active) {
+        const T* rx = A + q * SY + an * n;
+        T ym[4];
+        if constexpr (ROWLDS) {
+#pragma unroll
+          for (int nu = 0; nu < n; ++nu) rowx[nu] = A[kGsM + am * n + nu];
+        }
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+          T s = T(0), u = T(0);
+#pragma unroll
+          for (int nu = 0; nu < n; ++nu) s += rowx[nu] * rx[(8 + f) * SZ + nu];
+#pragma unroll
+          for (int nu = 0; nu < n; ++nu) u += rowx[nu] * rx[f * SZ + nu];
+          A[(12 + f) * SZ + q * SY + a] = s;
+          ym[f] = scale * u;
+          if constexpr (TIGHT) __builtin_amdgcn_sched_barrier(0);
+        }
+        Fy = face_sum<T>(tyy, ym[0], ym[2]);
+        Uy = face_sum<T>(tyy, ym[1], ym[3]);
+        Wy = face_sum<T>(tyy, A[0 * SZ + q * SY + a], A[2 * SZ + q * SY + a]);
+        // x-faces: one line per lane, on the last 4 E lanes
+        constexpr int first = TPP > 4 * E ? TPP - 4 * E : 0;
+#pragma unroll
+        for (int li0 = 0; li0 < 4 * E; li0 += TPP) {
+          const int li = li0 + lane - first;
+          if (li < 0 || li >= 4 * E) continue;
+          const int f = small_div<E>(li);
+          T* r = A + (4 + f) * SZ + (li - f * E) * SY;
+          Line<T> v, w;
+          load_line(r, 0, 1, v);
+          L1::ms(t, tyy, v, w);
+          store_line(r, 0, 1, w);
+        }
+        if constexpr (TIGHT) load_b();
+      }
+      __syncthreads();
+      // M_y on the z-layers; the x-faces of this lane's x-line (qy, qz) = (a, q)
+      if (active) {
+        const T* ry = A + qn * n * SY + a;
+        T zm[4], xm[4];
+        if constexpr (ROWLDS) {
+#pragma unroll
+          for (int nu = 0; nu < n; ++nu) rowy[nu] = A[kGsM + qm * n + nu];
+        }
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+          T s = T(0);
+#pragma unroll
+          for (int nu = 0; nu < n; ++nu) s += rowy[nu] * ry[(12 + f) * SZ + nu * SY];
+          zm[f] = scale * s;
+          xm[f] = A[(4 + f) * SZ + q * SY + a];
+          if constexpr (TIGHT) __builtin_amdgcn_sched_barrier(0);
+        }
+        Fl = face_sum<T>(tyl, zm[0], zm[2]);
+        Ul = face_sum<T>(tyl, zm[1], zm[3]);
+        Wx = face_sum<T>(tyx, xm[0], xm[2]);
+        Ux = face_sum<T>(tyx, scale * xm[1], scale * xm[3]);
+      }
+    } else {
+      // x-layers at py = lane, transformed by S_y^T M_y below
+      const bool xl = MODE == 2 || (tyx & 1), xrt = MODE == 2 || (tyx & 2);
+      T col[E];
+      if (active) {
+#pragma unroll
+        for (int p = 0; p < E; ++p) col[p] = at32(t->MS[tyl], (unsigned)(p * E + a));
+        const unsigned lx = (unsigned)an * cy + (unsigned)(n * am);
+        const T* xm = x0 - NC;
+        const T u0 = at32(xm, lx + NC), u2 = at32(xm, lx + 2 * NC + K);
+        const T u1 = xl ? u0 : at32(xm, lx + K), u3 = xrt ? u2 : at32(xm, lx + 3 * NC);
+        load_b();
+        if constexpr (WARM) warm_wait(warm);
+        A[4 * E + a] = u0;
+        A[5 * E + a] = u1;
+        A[6 * E + a] = u2;
+        A[7 * E + a] = u3;
+#pragma unroll
+        for (int f = 0; f < 4; ++f) A[f * E + a] = raw[f];
+      }
+      __syncthreads();
+      if (active) {
+        T ym[4], xm[4] = {T(0), T(0), T(0), T(0)};
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+          T s = T(0);
+#pragma unroll
+          for (int nu = 0; nu < n; ++nu) s += rowx[nu] * A[f * E + an * n + nu];
+          ym[f] = scale * s;
+        }
+        // col: this lane's eigenvector qy = a, its column of S^T M
+#pragma unroll
+        for (int p = 0; p < E; ++p) {
+#pragma unroll
+          for (int f = 0; f < 4; ++f) xm[f] += col[p] * A[(4 + f) * E + p];
+        }
+        Fl = face_sum<T>(tyl, ym[0], ym[2]);
+        Ul = face_sum<T>(tyl, ym[1], ym[3]);
+        Wx = face_sum<T>(tyx, xm[0], xm[2]);
+        Ux = face_sum<T>(tyx, scale * xm[1], scale * xm[3]);
+      }
+    }
+    Wl = face_sum<T>(tyl, raw[0], raw[2]);
+    __syncthreads();  // the tile takes the place of the face fields
+  } else {
+    if (active) load_b();
+    if constexpr (WARM) warm_wait(warm);
+  }
+  // where this lane's lines along x, y and the last direction start in the tile
+  const int bx = a * SY + q * SZ, by = a + q * SZ, bz = (D == 3) ? a + q * SY : a;
+  constexpr int sl = (D == 3) ? SZ : SY;
+  // last direction: S^T b - its faces
+  if (active) {
+    Line<T> o;
+    L1::fwd(t, tyl, bl, Fl, Ul, o);
+    store_line(A, bz, sl, o);
+  }
+  __syncthreads();
+  if constexpr (D == 3) {
+    if (active) {
+      Line<T> v, o;
+      load_line(A, by, SY, v);
+      L1::fwd(t, tyy, v, Fy, Uy, o);
+      store_line(A, by, SY, o);
+    }
+    __syncthreads();
+  }
+  if (active) {
+    // x-line (qy, qz) = (a, q) and its inverse eigenvalue sums
+    const T* rs = &at32(t->rs[0][(D == 3) ? (tyx * 4 + tyy) * 4 + tyl : tyx * 4 + tyy], (unsigned)lane);
+    Line<T> v, o;
+    load_line(A, bx, 1, v);
+    L1::turn(t, tyx, v, FacePair<T>{scale * Wx.s, scale * Wx.d}, Ux, Wx, inv_scale, rs, o);
+    store_line(A, bx, 1, o);
+  }
+  __syncthreads();
+  if constexpr (D == 3) {
+    if (active) {
+      Line<T> v, o;
+      load_line(A, by, SY, v);
+      L1::back(t, tyy, v, Wy, o);
+      store_line(A, by, SY, o);
+    }
+    __syncthreads();
+  }
+  // last direction back; only the nodes of V are written (ZERO: all of them,
+  // the others as the zeros they hold)
+  const bool keep_line = ZERO || ((a > 0 || (tyx & 1)) && (a < E - 1 || (tyx & 2)) &&
+                                  (D == 2 || ((q > 0 || (tyy & 1)) && (q < E - 1 || (tyy & 2)))));
+  if (active && keep_line) {
+    Line<T> v, o;
+    load_line(A, bz, sl, v);
+    L1::back(t, tyl, v, Wl, o);
+#pragma unroll
+    for (int p = 0; p < E; ++p) {
+      if (!ZERO && ((p == 0 && !(tyl & 1)) || (p == E - 1 && !(tyl & 2)))) continue;
+      at32(p < n ? x0 : x1, lo + (p % n) * ln) = o.v[p];
+    }
+  }
 }
 
 // One patch (pid of grid g, right-hand side rhs) of one colour; lane = thread
 // within the patch, sm = the patch's LDS.  Every thread of the workgroup calls
 // this (barriers inside), with pid >= g.npatch for idle slots.
-template <typename T, int MODE, bool PREFETCH, bool ZERO>
+// UNI: no wave holds lanes of patches of different types (the barriers of the
+// two paths it then may take are the same in number).
+template <typename T, int MODE, bool PREFETCH, bool ZERO, bool UNI = (TPP % 64 == 0)>
 __device__ __forceinline__ void smooth_body(const Tab<K, T>* __restrict__ t, const PatchGrid& g, T scale,
                                             T inv_scale, const T* __restrict__ xin, T* __restrict__ xout,
                                             const T* __restrict__ b, long long ndof, int pid, int lane,
                                             T* sm, int rhs) {
+  if constexpr (kDirect<MODE>) {
+    const bool act = pid < g.npatch;
+    // an idle slot of a right-hand-side-packed workgroup takes the position of
+    // the others: slots that share a wave have to take one path
+    const PatchPos Q = patch_pos(g, act ? pid : pid - g.npatch);
+    T* xv = xout + (long long)rhs * ndof;
+    const T* bv = b + (long long)rhs * ndof;
+    if (UNI && (Q.ty[0] | Q.ty[1] | Q.ty[2]) == 0)
+      gs_body<T, MODE, ZERO, true>(t, g.N, Q, scale, inv_scale, xv, bv, act, lane, sm);
+    else
+      gs_body<T, MODE, ZERO, false>(t, g.N, Q, scale, inv_scale, xv, bv, act, lane, sm);
+  } else {
   constexpr bool FULL = (MODE == 3);
   constexpr int SP = FULL ? SP_FULL : (MODE == 4) ? SP_CLAMPED : SP_DIR;
   constexpr int OPM = FULL ? 0 : (MODE == 4) ? 2 : MODE;  // operator-pass mode (side data)
@@ -1960,10 +2575,20 @@ __device__ __forceinline__ void smooth_body(const Tab<K, T>* __restrict__ t, con
       }
     }
   }
+  }
 }
 
+// Waves per SIMD the register allocation of k_smooth aims at (1: no aim): for
+// the direct form in 3-D the most an interior patch's passes allow without
+// spills.
+template <typename T, int MODE, int THREADS>
+constexpr int smooth_waves() {
+  if (D != 3 || !kDirect<MODE> || THREADS > 256) return 1;
+  if (sizeof(T) == 8) return K <= 4 ? 4 : 2;
+  return K <= 3 ? 8 : K == 4 ? 6 : K == 6 ? 4 : 5;
+}
 template <typename T, int PPB, int MODE, bool PREFETCH, bool ZERO = false, bool RP = false>
-__global__ void __launch_bounds__(TPP * PPB)
+__global__ void __launch_bounds__(TPP * PPB, (smooth_waves<T, MODE, TPP * PPB>()))
 k_smooth(const Tab<K, T>* __restrict__ t, PatchGrid g, T scale, T inv_scale,
          const T* __restrict__ xin, T* __restrict__ xout, const T* __restrict__ b, long long ndof) {
   constexpr int PP = smooth_pp<MODE>();
@@ -1971,16 +2596,18 @@ k_smooth(const Tab<K, T>* __restrict__ t, PatchGrid g, T scale, T inv_scale,
   const int slot = slot_of(), lane = threadIdx.x % TPP;
   int pid, rhs;
   slot_work<PPB, RP>(g, slot, pid, rhs);
-  smooth_body<T, MODE, PREFETCH, ZERO>(t, g, scale, inv_scale, xin, xout, b, ndof, pid, lane,
-                                       smem + slot * PP, rhs);
+  // one patch per workgroup, or one patch for all its slots
+  constexpr bool UNI = PPB == 1 || RP || TPP % 64 == 0;
+  smooth_body<T, MODE, PREFETCH, ZERO, UNI>(t, g, scale, inv_scale, xin, xout, b, ndof, pid, lane,
+                                            smem + slot * PP, rhs);
 }
 
 
 // ----------------------------------------------- split smoother (3-D)
-// The same colour step with two waves per patch (TPP a multiple of 64): wave h
-// of a patch owns, for every tile line, the outputs of cell h (indices
-// h n .. h n + n - 1) -- or the eigen-coefficients q in that range in the
-// fast-diagonalisation contractions -- while both waves read whole lines.
+// The clamped kernel's colour step with two waves per patch (TPP a multiple of
+// 64): wave h of a patch owns, for every tile line, the outputs of cell h
+// (indices h n .. h n + n - 1) -- or the eigen-coefficients q in that range in
+// the fast-diagonalisation contractions -- while both waves read whole lines.
 // The 1-D coefficients a wave needs stay wave-uniform, each output element is
 // computed with the operations of the one-wave kernel in the same order (so
 // the results are bitwise those of k_smooth), and a patch occupies twice the
@@ -2023,6 +2650,10 @@ __device__ __forceinline__ void half_mass(const Line<T>& v, Half<T>& o, bool nee
 template <typename T, int H, bool ACC>
 __device__ __forceinline__ void half_sipg(const Tab<K, T>* __restrict__ t, const Line<T>& v,
                                           const Sides<T>& sd, Half<T>& o, bool needEnd) {
+  if constexpr (kDiff<T>) {
+    cell_sipg_diff<T, H, ACC>(t->sigma, v, sd, o.v, needEnd, needEnd);
+    return;
+  }
   const T sg = t->sigma;
   const T half = T(0.5);
   T bl[n];
@@ -2092,7 +2723,7 @@ __device__ __forceinline__ void half_sipg(const Tab<K, T>* __restrict__ t, const
 template <typename T, int TY, int SP, int H>
 __device__ __forceinline__ void half_St_t(const Tab<K, T>* __restrict__ t, const Line<T>& v, Half<T>& o) {
   using B = FDB<SP, TY>;
-  const T* S = fd_S<T, SP>(t, TY);
+  const Coef<T> S = pass_coef<T, kOpaqueFD<T, SP>>(fd_S<T, SP>(t, TY));
   if constexpr (kEO && SP == SP_DIR && TY == 0) {
     T vp[kEOH], vm[kEOH];
     eo_split<T>(v, vp, vm);
@@ -2118,7 +2749,7 @@ __device__ __forceinline__ void half_St_t(const Tab<K, T>* __restrict__ t, const
 template <typename T, int TY, int SP, int H>
 __device__ __forceinline__ void half_S_t(const Tab<K, T>* __restrict__ t, const Line<T>& v, Half<T>& o) {
   using B = FDB<SP, TY>;
-  const T* S = fd_S<T, SP>(t, TY);
+  const Coef<T> S = pass_coef<T, kOpaqueFD<T, SP>>(fd_S<T, SP>(t, TY));
   if constexpr (kEO && SP == SP_DIR && TY == 0) {
 #pragma unroll
     for (int j = 0; j < n; ++j) {
@@ -2186,13 +2817,11 @@ __device__ __forceinline__ void smooth_split_body(const Tab<K, T>* __restrict__ 
                                                   T scale, T inv_scale, T* __restrict__ x,
                                                   const T* __restrict__ b, long long ndof, int pid,
                                                   int lane, T* sm, int rhs) {
-  static_assert(MODE != 3, "the Full kernel is not split");
-  constexpr int SP = (MODE == 4) ? SP_CLAMPED : SP_DIR;
-  constexpr int OPM = (MODE == 4) ? 2 : MODE;
+  static_assert(MODE == 4, "clamped kernel");
+  constexpr int SP = SP_CLAMPED;
   const bool active = pid < g.npatch;
   T* A = sm;
   T* B = A + TS;
-  T* ext = B + TS;
   const long long roff = (long long)rhs * ndof;
   T* xr = x + roff;
   const T* br = b + roff;
@@ -2219,72 +2848,16 @@ __device__ __forceinline__ void smooth_split_body(const Tab<K, T>* __restrict__ 
     }
     __syncthreads();
   } else {
-    // Q3: every global load of the first phases is issued here, before any
-    // of the values is used (one memory round trip instead of one per
-    // helper): the y-neighbour traces with their mass row, this lane's z-face
-    // trace, the x-line with its x-neighbour traces and the mass row of the
-    // z-sides.  For 16-point lines the registers this holds would cost a
-    // wave per SIMD, so there the helpers load one after the other.
-    static_assert(TPP == NF, "one z-face trace per lane of the two waves");
-    constexpr bool HOIST = (n <= 4);
+    // the clamped residual reads the patch cells alone: no traces of the
+    // neighbours, the sides only say where the domain boundary is
     Sides<T> ysd{}, sd{};
-    T zrow[n];
     Line<T> xl;
     const int py = lane % E, pz = lane / E;
     const long long row0 = xrow_offset(g.N, P, py, pz);
-    if constexpr (HOIST) {
-      YSideRaw<T> yraw;
-      T ztr = T(0), xtl = T(0), xtr = T(0);
-      const int zf = lane, zside = H;  // this lane's z-face entry (face node, side)
-      const int znb = (zside == 0) ? P.lo[2] - 1 : P.lo[2] + 2;
-      const bool zhas = MODE == 1 && znb >= 0 && znb < g.N;
-      const bool xbl = (P.lo[0] == 0), xbr = (P.lo[0] + 1 == g.N - 1);
-      if (active) {
-        yside_load<T, OPM>(xr, g.N, P, lane % E, lane / E, yraw);
-        if (MODE == 1) {
-          const int a = zf % E, bb = zf / E;
-          const long long base = cell_index(g.N, P.lo[0] + a / n, P.lo[1] + bb / n, zhas ? znb : P.lo[2]) * NC +
-                                 a % n + n * (bb % n);
-          ztr = xr[base + (long long)((zside == 0) ? K : 0) * n * n];
-        }
-        read_xline<T>(xr, row0, xl);
-        if (OPM != 2) {
-          xtl = xr[xbl ? row0 : row0 - NC + K];
-          xtr = xr[xbr ? row0 : row0 + 2 * NC];
-        }
-        mass_row<T>((lane / E) % n, zrow);
-        ysd = yside_finish<T, OPM>(yraw, g.N, P);
-        // z-face traces, spread over both waves (the register form of the
-        // one-wave kernel measured slower here: both waves would repeat it)
-        ext[zside * NF + zf] = zhas ? ((zside == 0) ? -T(0.5) * ztr : T(0.5) * ztr) : T(0);
-        // x-sides as xline_sides forms them for the smoother's residual
-        sd.bl = xbl;
-        sd.br = xbr;
-        sd.aL = sd.bL = sd.aR = sd.bR = T(0);
-        sd.lit = (OPM == 2);
-        if (OPM != 2) {
-          if (!sd.bl) sd.bL = -T(0.5) * xtl;
-          if (!sd.br) sd.bR = T(0.5) * xtr;
-        }
-      }
-    } else {
-      // this lane's z-face entry (face node lane, side H), its load issued
-      // before the y-side loads so that both arrive in one round trip
-      const int znb = (H == 0) ? P.lo[2] - 1 : P.lo[2] + 2;
-      const bool zhas = MODE == 1 && znb >= 0 && znb < g.N;
-      T ztr = T(0);
-      if (active && MODE == 1) {
-        const int a = lane % E, bb = lane / E;
-        const long long base = cell_index(g.N, P.lo[0] + a / n, P.lo[1] + bb / n, zhas ? znb : P.lo[2]) * NC +
-                               a % n + n * (bb % n);
-        ztr = xr[base + (long long)((H == 0) ? K : 0) * n * n];
-      }
-      if (active) ysd = yline_sides_global<T, OPM>(t, xr, g.N, P, lane % E, lane / E);
-      if (active) {
-        ext[H * NF + lane] = zhas ? ((H == 0) ? -T(0.5) * ztr : T(0.5) * ztr) : T(0);
-        read_xline<T>(xr, row0, xl);
-        sd = xline_sides<T, OPM>(t, xr, g.N, P, row0);
-      }
+    if (active) {
+      ysd = yline_sides_global<T, 2>(t, xr, g.N, P, lane % E, lane / E);
+      read_xline<T>(xr, row0, xl);
+      sd = xline_sides<T, 2>(t, xr, g.N, P, row0);
     }
     // X0: a = M_x x, b = L_x x on this half -> A, B
     if (active) {
@@ -2303,18 +2876,13 @@ __device__ __forceinline__ void smooth_split_body(const Tab<K, T>* __restrict__ 
     Half<T> c, d;
     int ybase = 0, ystride = 0;
     if (active) {
-      const int px = lane % E, pz = lane / E;
       line_geom(1, lane, ybase, ystride);
       Line<T> a, bl;
       load_line(A, ybase, ystride, a);
       load_line(B, ybase, ystride, bl);
-      (void)px;
-      (void)pz;
       half_mass<T, H>(bl, c, endy);
       half_sipg<T, H, true>(t, a, ysd, c, endy);
       half_mass<T, H>(a, d, endy);
-      // z-face traces contracted along x (16 rows, one per thread of wave 1)
-      if (H == 1 && lane < 2 * E) extz_mass_x_line<T, 1>(t, ext, lane);
     }
     __syncthreads();
     if (active) {
@@ -2324,19 +2892,15 @@ __device__ __forceinline__ void smooth_split_body(const Tab<K, T>* __restrict__ 
     __syncthreads();
     // Z: y = M_z c + L_z d, r = b - scale y on this half -> A, then S_z^T
     if (active) {
-      const int px = lane % E, py = lane / E;
       int base, stride;
       line_geom(2, lane, base, stride);
       Line<T> cl, dl;
       load_line(B, base, stride, cl);
       load_line(A, base, stride, dl);
-      Sides<T> sd;
-      if constexpr (HOIST) sd = zline_sides_row<T>(zrow, ext, g.N, P, px, py);
-      else sd = zline_sides<T, 1>(t, ext, g.N, P, px, py);
-      sd.lit = (OPM == 2);
+      const Sides<T> zsd{P.lo[2] == 0, P.lo[2] + 1 == g.N - 1, T(0), T(0), T(0), T(0), true};
       Half<T> y;
       half_mass<T, H>(cl, y, endz);
-      half_sipg<T, H, true>(t, dl, sd, y, endz);
+      half_sipg<T, H, true>(t, dl, zsd, y, endz);
       if (!PREFETCH) read_lasthalf<T>(br, g.N, P, lane, H, bh);
 #pragma unroll
       for (int j = 0; j < n; ++j) bh.v[j] -= scale * y.v[j];
@@ -2442,7 +3006,7 @@ template <typename T, int PPB, int MODE, bool PREFETCH, bool ZERO = false>
 __global__ void __launch_bounds__(2 * TPP * PPB)
 k_smooth_split(const Tab<K, T>* __restrict__ t, PatchGrid g, T scale, T inv_scale, T* __restrict__ x,
                const T* __restrict__ b, long long ndof) {
-  constexpr int PP = smooth_pp<1>();
+  constexpr int PP = smooth_pp<MODE>();
   __shared__ T smem[PPB * PP];
   const int w = (int)threadIdx.x / TPP;  // wave group: slot * 2 + half
   const int ws = kSplitOK ? __builtin_amdgcn_readfirstlane(w) : w;
@@ -2734,7 +3298,8 @@ k_coarse(const Tab<K, T>* __restrict__ t, T inv_scale, const T* __restrict__ b, 
 // exact coarse solve, prolongation + add, post-smoothing (descending).  Every
 // patch does the arithmetic of the separate kernels.  In-place smoothers only.
 constexpr int kBottomSlots = 1 << D;
-constexpr int kBottomPP = kRestrictPP > smooth_pp<1>() ? kRestrictPP : smooth_pp<1>();
+constexpr int max3(int a, int b, int c) { return a > b ? (a > c ? a : c) : (b > c ? b : c); }
+constexpr int kBottomPP = max3(kRestrictPP, smooth_pp<1>(), smooth_pp<4>());
 
 template <typename T>
 constexpr bool bottom_fits() {
@@ -2975,9 +3540,10 @@ hipError_t launch_mass(const void* tab, PatchGrid g, T scale, const T* x, T* y, 
                      (const Tab<K, T>*)tab, g, scale, x, y, ndof);
   return hipGetLastError();
 }
-// smoother shapes: bit 0 selects the workgroup shape, bit 1 the prefetch of b,
-// bit 2 two waves per patch where kSplitOK, else one patch per workgroup where
-// several patches share a wave (2-D, 3-D Q1: patches of different types there
+// smoother shapes: bit 0 selects the workgroup shape, bit 1 the prefetch of b
+// (not in the direct form, which has one order of loads), bit 2
+// two waves per patch where kSplitOK (clamped kernel), else one patch per
+// workgroup where several patches share a wave (2-D, 3-D Q1: patches of different types there
 // run their fast-diagonalisation branches one after the other), else the same
 // as bit 2 clear; variant 0 / 1 / 2 / 3: Dirichlet consistent / Dirichlet with
 // the paper's residual / Full / clamped
@@ -2993,6 +3559,7 @@ template <typename T, int R, bool PF>
 hipError_t launch_smooth_rpack(const Tab<K, T>* tb, PatchGrid g, T scale, T inv_scale, int variant,
                                int zero, const T* xin, T* xout, const T* b, int nrhs, long long ndof,
                                hipStream_t s) {
+  constexpr bool PFD = PF && !kDirect<1>;
   const dim3 grid(g.npatch, (nrhs + R - 1) / R), block(TPP * R);
   if (zero) {
     if (variant == 2)
@@ -3016,10 +3583,10 @@ hipError_t launch_smooth_rpack(const Tab<K, T>* tb, PatchGrid g, T scale, T inv_
     hipLaunchKernelGGL((k_smooth<T, R, 4, PF, false, true>), grid, block, 0, s, tb, g, scale, inv_scale,
                        xout, xout, b, ndof);
   else if (variant == 1)
-    hipLaunchKernelGGL((k_smooth<T, R, 2, PF, false, true>), grid, block, 0, s, tb, g, scale, inv_scale,
+    hipLaunchKernelGGL((k_smooth<T, R, 2, PFD, false, true>), grid, block, 0, s, tb, g, scale, inv_scale,
                        xout, xout, b, ndof);
   else
-    hipLaunchKernelGGL((k_smooth<T, R, 1, PF, false, true>), grid, block, 0, s, tb, g, scale, inv_scale,
+    hipLaunchKernelGGL((k_smooth<T, R, 1, PFD, false, true>), grid, block, 0, s, tb, g, scale, inv_scale,
                        xout, xout, b, ndof);
   return hipGetLastError();
 }
@@ -3027,7 +3594,7 @@ template <typename T, int V>
 hipError_t launch_smooth(const void* tab, PatchGrid g, T scale, T inv_scale, int variant, int zero,
                          const T* xin, T* xout, const T* b, int nrhs, long long ndof, hipStream_t s) {
   constexpr int PPB = (kOnePatchShape && (V & 4)) ? 1 : Shape<(V & 1)>::PPB;
-  constexpr bool PF = (V & 2) != 0;
+  constexpr bool PF = (V & 2) != 0, PFD = PF && !kDirect<1>;
   constexpr bool SPLIT = (V & 4) != 0 && kSplitOK;
   g.nrhs = nrhs;
   const Tab<K, T>* tb = (const Tab<K, T>*)tab;
@@ -3038,28 +3605,14 @@ hipError_t launch_smooth(const void* tab, PatchGrid g, T scale, T inv_scale, int
   }
   dim3 grid((g.npatch + PPB - 1) / PPB, nrhs);
   if constexpr (SPLIT) {
-    if (variant != 2) {
+    if (variant == 3) {
       const dim3 block(2 * TPP * PPB);
-      if (zero) {
-        if (variant == 3)
-          hipLaunchKernelGGL((k_smooth_split<T, PPB, 4, false, true>), grid, block, 0, s, tb, g, scale,
-                             inv_scale, xout, b, ndof);
-        else if (variant == 1)
-          hipLaunchKernelGGL((k_smooth_split<T, PPB, 2, false, true>), grid, block, 0, s, tb, g, scale,
-                             inv_scale, xout, b, ndof);
-        else
-          hipLaunchKernelGGL((k_smooth_split<T, PPB, 1, false, true>), grid, block, 0, s, tb, g, scale,
-                             inv_scale, xout, b, ndof);
-      } else if (variant == 3) {
+      if (zero)
+        hipLaunchKernelGGL((k_smooth_split<T, PPB, 4, false, true>), grid, block, 0, s, tb, g, scale,
+                           inv_scale, xout, b, ndof);
+      else
         hipLaunchKernelGGL((k_smooth_split<T, PPB, 4, PF>), grid, block, 0, s, tb, g, scale, inv_scale,
                            xout, b, ndof);
-      } else if (variant == 1) {
-        hipLaunchKernelGGL((k_smooth_split<T, PPB, 2, PF>), grid, block, 0, s, tb, g, scale, inv_scale,
-                           xout, b, ndof);
-      } else {
-        hipLaunchKernelGGL((k_smooth_split<T, PPB, 1, PF>), grid, block, 0, s, tb, g, scale, inv_scale,
-                           xout, b, ndof);
-      }
       return hipGetLastError();
     }
   }
@@ -3085,10 +3638,10 @@ hipError_t launch_smooth(const void* tab, PatchGrid g, T scale, T inv_scale, int
     hipLaunchKernelGGL((k_smooth<T, PPB, 4, PF>), grid, dim3(TPP * PPB), 0, s, tb, g, scale,
                        inv_scale, xout, xout, b, ndof);
   else if (variant == 1)
-    hipLaunchKernelGGL((k_smooth<T, PPB, 2, PF>), grid, dim3(TPP * PPB), 0, s, tb, g, scale,
+    hipLaunchKernelGGL((k_smooth<T, PPB, 2, PFD>), grid, dim3(TPP * PPB), 0, s, tb, g, scale,
                        inv_scale, xout, xout, b, ndof);
   else
-    hipLaunchKernelGGL((k_smooth<T, PPB, 1, PF>), grid, dim3(TPP * PPB), 0, s, tb, g, scale,
+    hipLaunchKernelGGL((k_smooth<T, PPB, 1, PFD>), grid, dim3(TPP * PPB), 0, s, tb, g, scale,
                        inv_scale, xout, xout, b, ndof);
   return hipGetLastError();
 }
@@ -3136,12 +3689,8 @@ hipError_t launch_bottom(const void* tab, int variant, int split, T scale1, T in
     const Tab<K, T>* tb = (const Tab<K, T>*)tab;
     const dim3 grid(1, nrhs), block(TPP * kBottomSlots);
     if constexpr (kBottomSplitOK) {
-      if (split) {
-        const dim3 block2(2 * TPP * kBottomSlots);
-        if (variant == 0) hipLaunchKernelGGL((k_bottom_split<T, 1>), grid, block2, 0, s, tb, a);
-        else if (variant == 1) hipLaunchKernelGGL((k_bottom_split<T, 2>), grid, block2, 0, s, tb, a);
-        else if (variant == 3) hipLaunchKernelGGL((k_bottom_split<T, 4>), grid, block2, 0, s, tb, a);
-        else return hipErrorInvalidValue;
+      if (split && variant == 3) {
+        hipLaunchKernelGGL((k_bottom_split<T, 4>), grid, dim3(2 * TPP * kBottomSlots), 0, s, tb, a);
         return hipGetLastError();
       }
     }
@@ -3204,6 +3753,7 @@ KernelSet<T> make_set() {
   k.smooth[11] = &launch_smooth<T, 11>;
   k.smooth_split = (kSplitOK || kOnePatchShape) ? 1 : 0;
   k.smooth_hi_full = kOnePatchShape ? 1 : 0;
+  k.smooth_direct = kDirect<1> ? 1 : 0;
   k.restrict_residual = &launch_restrict<T>;
   k.prolongate_add = &launch_prolong<T>;
   k.coarse = &launch_coarse<T>;

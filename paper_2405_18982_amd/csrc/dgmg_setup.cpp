@@ -181,6 +181,36 @@ std::vector<double> clamped_basis(int k, int t, const std::vector<double>& d0,
   return Cb;
 }
 
+// MS, gp, gt, gm of patch type t (HostTables) from its eigenpairs and the 1-D
+// patch matrices L, M.
+void line_couplings(int t, const std::vector<double>& L, const std::vector<double>& Mp, HostTables& T) {
+  const int n = T.n, E = T.E;
+  T.MS[t].assign(E * E, 0.0);
+  for (std::vector<double>* g : {&T.gp[t], &T.gt[t], &T.gm[t]}) g->assign(E, 0.0);
+  const bool left = !(t & 1), right = !(t & 2);  // dropped ends
+  const int c = left ? 0 : E - 1;
+  for (int q = 0; q < E; ++q) {
+    if (std::isinf(T.lam[t][q])) continue;
+    for (int p = 0; p < E; ++p) {
+      long double s = 0;
+      for (int i = 0; i < E; ++i) s += (long double)T.S[t][i * E + q] * Mp[i * E + p];
+      T.MS[t][p * E + q] = (double)s;
+    }
+    if (!left && !right) continue;
+    long double sl = 0, sm = 0, sg = 0;
+    for (int i = 0; i < E; ++i) {  // S is zero on dropped nodes
+      sl += (long double)T.S[t][i * E + q] * L[i * E + c];
+      sm += (long double)T.S[t][i * E + q] * Mp[i * E + c];
+    }
+    // the trace u of the cell beyond enters row i as -d0_i u / 2 (left), d1_i u / 2 (right)
+    for (int a = 0; a < n; ++a)
+      sg += left ? -0.5L * T.S[t][a * E + q] * T.d0[a] : 0.5L * T.S[t][(n + a) * E + q] * T.d1[a];
+    T.gm[t][q] = (double)sm;
+    T.gp[t][q] = (double)(sl - (long double)T.lam[t][q] * sm);
+    T.gt[t][q] = (double)sg;
+  }
+}
+
 }  // namespace
 
 template <int K>
@@ -297,6 +327,7 @@ bool build_host_tables(int k, double sigma, HostTables& T, const char** err) {
       }
       if (!patch_eigenpairs(L, Mp, E, keep, T.S[t], T.lam[t], err)) return false;
     }
+    line_couplings(t, L, Mp, T);
     // Full kernel: every node of the two cells
     std::vector<int> all(E);
     for (int p = 0; p < E; ++p) all[p] = p;

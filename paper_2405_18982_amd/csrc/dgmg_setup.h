@@ -18,6 +18,18 @@ struct HostTables {
   // S[t][p*E + q], lam[t][q] (+inf in unused slots)
   std::vector<double> S[4];
   std::vector<double> lam[4];
+  // couplings of the Dirichlet space (kept nodes V) to the rest of the line in
+  // the eigenbasis, per patch type; c the dropped end node (type 0: the left
+  // one; the right one has the same entries, sign changed for the odd
+  // eigenvectors q >= k):
+  //   MS[t][p*E + q] = (S^T M)[q][p]              every node p
+  //   gm[t][q] = (S^T M e_c)[q]
+  //   gp[t][q] = (S^T L e_c)[q] - lam[q] gm[q]    so that on the whole line
+  //              S^T L v = Lambda S^T M v + gp v_c (+ gt times the outer trace)
+  //   gt[t][q] = (S^T g)[q], g the coupling of V to the trace of the cell
+  //              beyond the dropped end
+  // (zero in unused slots and for type 3, which drops no node)
+  std::vector<double> MS[4], gp[4], gt[4], gm[4];
   // the same on the whole two-cell patch (Full kernel; every slot used)
   std::vector<double> Sf[4];
   std::vector<double> lamf[4];
