@@ -240,10 +240,14 @@ struct Sides {
 // of a cell act on its values less one of them (their rows sum to zero, so a
 // column drops out), the face terms on jumps.  With the values themselves the
 // rounding of the coefficients acts like a small reaction term: the FP32
-// V-cycles of Q5..Q7 on random loads were off by 1e-6..4e-5.  FP64 keeps the
-// plain rows.
+// V-cycles of Q5..Q7 on random loads were off by 1e-6..4e-5.  The shortest lines
+// keep the plain rows: 2-D Q1, and 3-D up to Q3, whose V-cycles on plain rows
+// are off by 2e-7..7e-7 (on differences 2e-7..5e-7) and whose FP32 operator is
+// 3-6% faster on them (3-D Q3 8^3 4.13 / 4.39 us, 32^3 8.1 / 8.4 us, Q1 64^3
+// restriction 11.1 / 11.8 us); 2-D Q2, Q3 would be off by up to 1.6e-6.  FP64
+// keeps the plain rows.
 template <typename T>
-constexpr bool kDiff = sizeof(T) == 4;
+constexpr bool kDiff = sizeof(T) == 4 && K >= (D == 3 ? 4 : 2);
 
 // alpha of a face from the neighbour's derivative g and trace tr; on
 // differences the penalty part is left to the line, which forms the jump
@@ -508,9 +512,9 @@ __device__ __forceinline__ void load_rs(const Tab<K, T>* __restrict__ t, const i
 // eigenvectors on the even and the odd subspace (columns q < h even,
 // h <= q < 2h odd, h = n - 1).  S^T then contracts sums v+ and differences v-
 // of mirrored nodes with half columns, and S forms the even part e and odd
-// part d of each mirrored pair: 2 h^2 multiply-adds instead of 4 h^2.  Used
-// from Q4 on: measured on a smoothing step, 4-12% faster for Q4..Q7, 4-5%
-// slower for Q3 (h = 3), where the dense contraction stays.
+// part d of each mirrored pair: 2 h^2 multiply-adds instead of 4 h^2 (a wave of
+// an interior Q3 patch in FP64: 970 vector instructions without, 472 with it
+// and the compile-time patch type).
 constexpr int kEOH = n - 1;
 constexpr bool kEO = (K >= 2);
 
@@ -1043,11 +1047,12 @@ __device__ __forceinline__ void read_xline(const T* __restrict__ x, long long ro
 // held one per lane can be contracted across lanes.
 constexpr bool kZShfl = (TPP <= 64) && (64 % TPP == 0);
 
-// sum_nu row[nu] v(lane + E (nu - mu)): the y-contraction of z-face values
-// held one per lane (wl: the lane's index in its wave)
-template <typename T>
+// sum_nu row[nu] v(lane + LQ (nu - mu)): the y-contraction of z-face values
+// held one per lane (wl: the lane's index in its wave; LQ: lanes between nodes
+// consecutive in y)
+template <typename T, int LQ = E>
 __device__ __forceinline__ T ycontract_lanes(const T (&row)[n], T v, int wl, int mu) {
-  return face_dot<T>(row, [&](int nu) { return __shfl(v, wl + E * (nu - mu), 64); });
+  return face_dot<T>(row, [&](int nu) { return __shfl(v, wl + LQ * (nu - mu), 64); });
 }
 
 // Couplings (alpha, beta) of one face node of a neighbour cell across a y-
@@ -1488,22 +1493,33 @@ k_apply(const Tab<K, T>* __restrict__ t, PatchGrid g, T scale, const T* __restri
 }
 
 // ------------------------------------------- apply, face data in registers
-// The face data of the y- and z-neighbours need not be gathered per face node
-// into LDS.  Lane l forms, for its y-line (px, pz) and for the z-face node
-// (px, py) of the same lane number, the couplings alpha, beta of the n face
-// nodes of its x-block from the neighbour's lines along the face normal, and
-// contracts them with the mass row of px in registers.  The z-face values are
-// then contracted along y: where the lines of a patch sit in one wave (Q1,
-// Q3: TPP = 16 or 64 lanes) with the lanes of the same px in the y-block
-// (lane offsets E (nu - mu), cross-lane reads), otherwise through a small LDS
-// array of the x-contracted values.  Every value is the expression of
-// gather_ext / ext_mx / extz_mass_x_line / ext_my in the same order, so the
-// result equals k_apply bit for bit.  LDS per patch: the two tiles (Q3 in
-// FP64: 9 KB instead of 13 KB, 16 patches per CU instead of 12), plus
-// 4 E^2 values elsewhere (Q7 in FP64: 78 KB instead of 86 KB, two patches per
-// CU instead of one).
+// Each lane forms the couplings alpha, beta of one node of each y- and z-face
+// from its own node column of the neighbour (n values along the normal), and
+// the mass contractions along x and y run across lanes where a patch's lines
+// sit in one wave (Q1, Q3: TPP = 16 or 64 lanes), otherwise through LDS (12
+// values a face node, in the space the tiles take afterwards).  The sums are
+// those of gather_ext / ext_mx / extz_mass_x_line / ext_my in the same order,
+// so the result equals k_apply bit for bit.
+// What bounds it: memory requests, then wavefronts in flight.  The lanes run
+// through a plane cell by cell and the z-lines go straight from registers to
+// memory, n^2 consecutive values a cell: written row by row from a tile, a
+// wave's 16-byte pieces cost four times the write requests of the values (Q7
+// FP64: 512 a wave instead of 128) and a phase more.  Measured on 32^3 cells,
+// x-rows out / z-lines out: Q4 x 16 right-hand sides FP64 394 / 356 us, FP32 234 /
+// 211 us; Q6 79 / 76 us; Q7 113 / 98 us.
+// One tile where two leave fewer than four patches of four waves a CU (Q7 in
+// FP64: 70 KB): M_x x goes through it to the y-lines, then L_x x, likewise the
+// two y-results; two barriers more each, three patches a CU instead of two: 98 /
+// 91 us (64^3: 839 us on two tiles with x-rows out, 711 us now, 3.0 TB/s of
+// the 2.1 GB it reads and writes).  For the other degrees one tile measured the same or up to 2%
+// slower.
 constexpr bool kApplyRF = (D == 3);
-constexpr int kApplyRFPP = 2 * TS + (kZShfl ? 0 : 4 * NF);
+template <typename T>
+constexpr bool kApplyOne = 2 * TS * (int)sizeof(T) > 64 * 1024;
+template <typename T>
+constexpr int kApplyTiles = kApplyOne<T> ? TS : 2 * TS;
+template <typename T>
+constexpr int kApplyRFPP = kZShfl || kApplyTiles<T> > 12 * NF ? kApplyTiles<T> : 12 * NF;
 
 template <typename T>
 __device__ __forceinline__ void restrict_tail(const PatchGrid& g, const PatchPos& P, T* A, T* __restrict__ bc,
@@ -1518,8 +1534,7 @@ __device__ __forceinline__ void restrict_tail(const PatchGrid& g, const PatchPos
 //     (the operator output and the P^T contractions in the same order);
 //   RF_EMIT: emit(l, base, stride, v) with the operator output v of z-line l
 //     (as operator_passes hands it to the Full smoother), nothing after it.
-// All on the smaller LDS footprint of this kernel (two tiles, plus four
-// z-face rows where patches span several waves).
+// All on the smaller LDS footprint of this kernel (kApplyRFPP).
 constexpr int RF_APPLY = 0, RF_RESTRICT = 1, RF_EMIT = 2;
 template <typename T, int OUT, typename Emit = int>
 __device__ __forceinline__ void apply_rf_body(const Tab<K, T>* t, const PatchGrid& g, T scale, const T* x, T* y,
@@ -1528,16 +1543,22 @@ __device__ __forceinline__ void apply_rf_body(const Tab<K, T>* t, const PatchGri
   // cross-lane reads stay within a patch's lanes, which lie in one wave
   static_assert(kApplyRF, "3-D only");
   const int wl = threadIdx.x & 63;
-  T* B = A + TS;
+  T* B = kApplyOne<T> ? A : A + TS;
   const long long roff = (long long)rhs * ndof;
   const T* xr = x + roff;
   const int N = g.N;
   const PatchPos P = patch_pos(g, active ? pid : 0);
-  // lane = px + E q: y-line (px, pz = q), z-face node (px, py = q)
-  const int px = lane % E, q = lane / E;
+  // this lane's lines: x (py = px, pz = q), y (px, pz = q), z (px, py = q) and
+  // its face nodes of the same numbers; the lanes run through a plane cell by
+  // cell (RF_EMIT: row by row, the order of its caller's lines)
+  constexpr bool CM = OUT != RF_EMIT;
+  constexpr int LQ = CM ? n : E;  // lanes from one q to the next within a cell
+  const int px = CM ? (lane / (n * n)) % 2 * n + lane % n : lane % E;
+  const int q = CM ? lane / (2 * n * n) * n + lane / n % n : lane / E;
+  const int ln = px + E * q;
   T rowx[n], rowy[n];
   face_row<T>(px % n, rowx);
-  face_row<T>(q % n, rowy);
+  if constexpr (kFaceDPP) face_row<T>(q % n, rowy);
   const bool ybl = (P.lo[1] == 0), ybr = (P.lo[1] + 1 == N - 1);
   const bool zbl = (P.lo[2] == 0), zbr = (P.lo[2] + 1 == N - 1);
   T ya0 = T(0), yb0 = T(0), ya1 = T(0), yb1 = T(0);
@@ -1576,8 +1597,7 @@ __device__ __forceinline__ void apply_rf_body(const Tab<K, T>* t, const PatchGri
         fz1[j] = c1[j * n * n];
       }
     }
-    const int py = lane % E, pz = lane / E;
-    const long long row0 = xrow_offset(N, P, py, pz);
+    const long long row0 = xrow_offset(N, P, px, q);
     read_xline<T>(xr, row0, xl);
     const bool xbl = (P.lo[0] == 0), xbr = (P.lo[0] + 1 == N - 1);
     T rl[n], rr[n];
@@ -1614,44 +1634,68 @@ __device__ __forceinline__ void apply_rf_body(const Tab<K, T>* t, const PatchGri
     fc[6] = xcontract_lanes<T>(rowx, nza1), fc[7] = xcontract_lanes<T>(rowx, nzb1);
   } else {
     __syncthreads();
+    // (read only now: with the first loads they cost Q7 in FP64 its third wave)
+    face_row<T>(q % n, rowy);
     if (active) {
       const T* w = A + lane - nuo;
 #pragma unroll
       for (int f = 0; f < 8; ++f) fc[f] = face_dot<T>(rowx, [&](int nu) { return w[f * NF + nu]; });
     }
-    __syncthreads();
   }
   if (active) {
     if (!ybl) { ya0 = fc[0]; yb0 = fc[1]; }
     if (!ybr) { ya1 = fc[2]; yb1 = fc[3]; }
     if (!zbl) { za0 = fc[4]; zb0 = fc[5]; }
     if (!zbr) { za1 = fc[6]; zb1 = fc[7]; }
-    // X0: a = M_x x -> A, b = L_x x -> B
-    int base, stride;
-    line_geom(0, lane, base, stride);
-    Line<T> a, b;
-    line_mass<T>(t, xl, a);
-    line_sipg<T, false>(t, xl, xsd, b);
-    store_line(A, base, stride, a);
-    store_line(B, base, stride, b);
   }
-  if constexpr (!kZShfl) {  // x-contracted z-face values for the y-contraction
+  const int muy = q % n;
+  T zaL = T(0), zbL = T(0), zaR = T(0), zbR = T(0);
+  if constexpr (kZShfl) {  // (all lanes of a patch take part)
+    zaL = ycontract_lanes<T, LQ>(rowy, za0, wl, muy);
+    zbL = ycontract_lanes<T, LQ>(rowy, zb0, wl, muy);
+    zaR = ycontract_lanes<T, LQ>(rowy, za1, wl, muy);
+    zbR = ycontract_lanes<T, LQ>(rowy, zb1, wl, muy);
+  } else {
+    T* wz = A + 8 * NF;  // beyond the node couplings, which may still be read
     if (active) {
-      T* wz = B + TS;
       wz[0 * NF + lane] = za0;
       wz[1 * NF + lane] = zb0;
       wz[2 * NF + lane] = za1;
       wz[3 * NF + lane] = zb1;
     }
+    __syncthreads();
+    if (active) {
+      const int f0 = lane - LQ * muy;
+      auto zrow = [&](int f) { return face_dot<T>(rowy, [&](int nu) { return wz[f * NF + f0 + LQ * nu]; }); };
+      zaL = zrow(0);
+      zbL = zrow(1);
+      zaR = zrow(2);
+      zbR = zrow(3);
+    }
+    __syncthreads();
+  }
+  int bx, sx, by, sy, base, stride;
+  line_geom(0, ln, bx, sx);
+  line_geom(1, ln, by, sy);
+  line_geom(2, ln, base, stride);
+  Line<T> la, lb, lc, ld, o;
+  // X: a = M_x x, b = L_x x
+  if (active) {
+    line_mass<T>(t, xl, la);
+    line_sipg<T, false>(t, xl, xsd, lb);
+    store_line(A, bx, sx, la);
+    if constexpr (!kApplyOne<T>) store_line(B, bx, sx, lb);
   }
   __syncthreads();
-  // Y: c = M_y b + L_y a -> B, d = M_y a -> A
+  // Y: c = M_y b + L_y la, d = M_y a
+  if (active) load_line(A, by, sy, la);
+  if constexpr (kApplyOne<T>) {
+    __syncthreads();
+    if (active) store_line(A, bx, sx, lb);
+    __syncthreads();
+  }
   if (active) {
-    int base, stride;
-    line_geom(1, lane, base, stride);
-    Line<T> a, b, c, d;
-    load_line(A, base, stride, a);
-    load_line(B, base, stride, b);
+    load_line(B, by, sy, lb);
     Sides<T> sd;
     sd.bl = ybl;
     sd.br = ybr;
@@ -1660,40 +1704,22 @@ __device__ __forceinline__ void apply_rf_body(const Tab<K, T>* t, const PatchGri
     sd.aR = ya1;
     sd.bR = yb1;
     sd.lit = false;
-    line_mass<T>(t, b, c);
-    line_sipg<T, true>(t, a, sd, c);
-    line_mass<T>(t, a, d);
-    store_line(B, base, stride, c);
-    store_line(A, base, stride, d);
-  }
-  // z-face values contracted along y (all lanes of a patch take part)
-  const int muy = q % n;
-  T zaL = T(0), zbL = T(0), zaR = T(0), zbR = T(0);
-  if constexpr (kZShfl) {
-    zaL = ycontract_lanes<T>(rowy, za0, wl, muy);
-    zbL = ycontract_lanes<T>(rowy, zb0, wl, muy);
-    zaR = ycontract_lanes<T>(rowy, za1, wl, muy);
-    zbR = ycontract_lanes<T>(rowy, zb1, wl, muy);
+    line_mass<T>(t, lb, lc);
+    line_sipg<T, true>(t, la, sd, lc);
+    line_mass<T>(t, la, ld);
+    store_line(B, by, sy, lc);
+    if constexpr (!kApplyOne<T>) store_line(A, by, sy, ld);
   }
   __syncthreads();
-  if constexpr (!kZShfl) {
-    if (active) {
-      const T* wz = B + TS;
-      const int f0 = px + E * (q - muy);
-      auto zrow = [&](int f) { return face_dot<T>(rowy, [&](int nu) { return wz[f * NF + f0 + E * nu]; }); };
-      zaL = zrow(0);
-      zbL = zrow(1);
-      zaR = zrow(2);
-      zbR = zrow(3);
-    }
-  }
   // Z: y = M_z c + L_z d
+  if (active) load_line(B, base, stride, lc);
+  if constexpr (kApplyOne<T>) {
+    __syncthreads();
+    if (active) store_line(A, by, sy, ld);
+    __syncthreads();
+  }
   if (active) {
-    int base, stride;
-    line_geom(2, lane, base, stride);
-    Line<T> c, d, o;
-    load_line(B, base, stride, c);
-    load_line(A, base, stride, d);
+    load_line(A, base, stride, ld);
     Sides<T> sd;
     sd.bl = zbl;
     sd.br = zbr;
@@ -1702,14 +1728,14 @@ __device__ __forceinline__ void apply_rf_body(const Tab<K, T>* t, const PatchGri
     sd.aR = zbr ? T(0) : zaR;
     sd.bR = zbr ? T(0) : zbR;
     sd.lit = false;
-    line_mass<T>(t, c, o);
-    line_sipg<T, true>(t, d, sd, o);
+    line_mass<T>(t, lc, o);
+    line_sipg<T, true>(t, ld, sd, o);
     if constexpr (OUT == RF_EMIT) {
-      emit(lane, base, stride, o);
+      emit(ln, base, stride, o);
     } else if constexpr (OUT == RF_RESTRICT) {
       // r = b - scale A x on this z-line, contracted with P^T along z
       Line<T> r;
-      read_lastline<T>(b + roff, N, P, lane, r);
+      read_lastline<T>(b + roff, N, P, ln, r);
 #pragma unroll
       for (int nu = 0; nu < n; ++nu) {
         T s = T(0);
@@ -1718,28 +1744,16 @@ __device__ __forceinline__ void apply_rf_body(const Tab<K, T>* t, const PatchGri
         A[base + nu * stride] = s;
       }
     } else {
+      // straight to memory: the lanes of a cell write n^2 consecutive values
+      T* yz = y + roff + node_offset(N, P, px, q, 0);
+      const long long cz = (long long)N * N * NC;
 #pragma unroll
-      for (int p = 0; p < E; ++p) A[base + p * stride] = scale * o.v[p];
+      for (int p = 0; p < E; ++p) yz[(p / n) * cz + (p % n) * (n * n)] = scale * o.v[p];
     }
   }
-  if constexpr (OUT == RF_EMIT) return;  // the caller's barrier follows
-  __syncthreads();
   if constexpr (OUT == RF_RESTRICT) {
+    __syncthreads();
     restrict_tail<T>(g, P, A, y, ndof_c, rhs, lane, active);
-  } else {
-    // X2: contiguous row stores
-    if (active) {
-      T* yr = y + roff;
-      const int py = lane % E, pz = lane / E;
-      int base, stride;
-      line_geom(0, lane, base, stride);
-      const long long row0 = xrow_offset(N, P, py, pz);
-#pragma unroll
-      for (int a = 0; a < n; ++a) {
-        yr[row0 + a] = A[base + a];
-        yr[row0 + NC + a] = A[base + n + a];
-      }
-    }
   }
 }
 
@@ -1747,12 +1761,12 @@ template <typename T, int PPB, bool RP = false>
 __global__ void __launch_bounds__(TPP * PPB)
 k_apply_rf(const Tab<K, T>* __restrict__ t, PatchGrid g, T scale, const T* __restrict__ x,
            T* __restrict__ y, long long ndof) {
-  __shared__ T smem[PPB * kApplyRFPP];
+  __shared__ T smem[PPB * kApplyRFPP<T>];
   const int slot = slot_of(), lane = threadIdx.x % TPP;
   int pid, rhs;
   slot_work<PPB, RP>(g, slot, pid, rhs);
   Line<T> xl;
-  apply_rf_body<T, RF_APPLY>(t, g, scale, x, y, nullptr, ndof, 0, pid, lane, smem + slot * kApplyRFPP, rhs,
+  apply_rf_body<T, RF_APPLY>(t, g, scale, x, y, nullptr, ndof, 0, pid, lane, smem + slot * kApplyRFPP<T>, rhs,
                              pid < g.npatch, xl);
 }
 
@@ -1847,10 +1861,10 @@ constexpr bool kDirect = (MODE == 1 || MODE == 2) && direct_smoother(D, K);
 // In 3-D the mass matrix follows where n > 4.
 constexpr int kGsM = (16 > E ? 16 : E) * SZ;
 constexpr int kGsPP = (D == 3) ? kGsM + (n > 4 ? n * n : 0) : (TS > 8 * E ? TS : 8 * E);
-template <int MODE>
+template <int MODE, typename T = double>
 __host__ __device__ constexpr int smooth_pp() {
   return kDirect<MODE> ? kGsPP
-         : MODE == 3 ? (kFullRF ? 2 * TS : kFullOnApplyRF ? kApplyRFPP : Smem<2, (D - 1) * 2 * 2 * NF>::per_patch)
+         : MODE == 3 ? (kFullRF ? 2 * TS : kFullOnApplyRF ? kApplyRFPP<T> : Smem<2, (D - 1) * 2 * 2 * NF>::per_patch)
                    : Smem<2, (D - 2) * 2 * NF>::per_patch;
 }
 
@@ -2591,7 +2605,7 @@ template <typename T, int PPB, int MODE, bool PREFETCH, bool ZERO = false, bool 
 __global__ void __launch_bounds__(TPP * PPB, (smooth_waves<T, MODE, TPP * PPB>()))
 k_smooth(const Tab<K, T>* __restrict__ t, PatchGrid g, T scale, T inv_scale,
          const T* __restrict__ xin, T* __restrict__ xout, const T* __restrict__ b, long long ndof) {
-  constexpr int PP = smooth_pp<MODE>();
+  constexpr int PP = smooth_pp<MODE, T>();
   __shared__ T smem[PPB * PP];
   const int slot = slot_of(), lane = threadIdx.x % TPP;
   int pid, rhs;
@@ -3006,7 +3020,7 @@ template <typename T, int PPB, int MODE, bool PREFETCH, bool ZERO = false>
 __global__ void __launch_bounds__(2 * TPP * PPB)
 k_smooth_split(const Tab<K, T>* __restrict__ t, PatchGrid g, T scale, T inv_scale, T* __restrict__ x,
                const T* __restrict__ b, long long ndof) {
-  constexpr int PP = smooth_pp<MODE>();
+  constexpr int PP = smooth_pp<MODE, T>();
   __shared__ T smem[PPB * PP];
   const int w = (int)threadIdx.x / TPP;  // wave group: slot * 2 + half
   const int ws = kSplitOK ? __builtin_amdgcn_readfirstlane(w) : w;
@@ -3113,19 +3127,18 @@ k_restrict(const Tab<K, T>* __restrict__ t, PatchGrid g, T scale, const T* __res
 }
 
 // 3-D degrees whose patches span several waves (or do not divide one): the
-// same restriction on the register-face operator of k_apply_rf, whose LDS
-// holds two tiles and four z-face rows instead of the face arrays (3-D Q7 in
-// FP64: two patches per CU instead of one)
+// same restriction on the register-face operator of k_apply_rf (3-D Q7 in
+// FP64, 32^3: 120 us on two tiles, 105 us on its one)
 constexpr bool kRestrictOnApplyRF = kApplyRF && !kRestrictRF;
 template <typename T, int PPB>
 __global__ void __launch_bounds__(TPP * PPB)
 k_restrict_rf(const Tab<K, T>* __restrict__ t, PatchGrid g, T scale, const T* __restrict__ x,
               const T* __restrict__ b, T* __restrict__ bc, long long ndof, long long ndof_c) {
-  __shared__ T smem[PPB * kApplyRFPP];
+  __shared__ T smem[PPB * kApplyRFPP<T>];
   const int slot = slot_of(), lane = threadIdx.x % TPP;
   const int pid = xcd_block(blockIdx.x, gridDim.x, g.xcd_remap) * PPB + slot;
   Line<T> xl;
-  apply_rf_body<T, RF_RESTRICT>(t, g, scale, x, bc, b, ndof, ndof_c, pid, lane, smem + slot * kApplyRFPP,
+  apply_rf_body<T, RF_RESTRICT>(t, g, scale, x, bc, b, ndof, ndof_c, pid, lane, smem + slot * kApplyRFPP<T>,
                                 blockIdx.y, pid < g.npatch, xl);
 }
 
@@ -3486,7 +3499,7 @@ constexpr int rpack_slots() {
 }
 template <typename T>
 constexpr int rpack_apply_slots() {
-  return kApplyRF ? rpack_slots<T, kApplyRFPP>()
+  return kApplyRF ? rpack_slots<T, kApplyRFPP<T>>()
                   : rpack_slots<T, Smem<2, (D - 1) * 2 * 2 * NF>::per_patch>();
 }
 
@@ -3552,7 +3565,7 @@ constexpr bool kOnePatchShape = !kSplitOK && PPB_DEFAULT > 1;
 // bit 0 selecting the larger slot count, bit 1 the prefetch of b
 template <typename T>
 constexpr int rpack_smooth_slots(bool large) {
-  constexpr int r = rpack_slots<T, smooth_pp<3>()>();
+  constexpr int r = rpack_slots<T, smooth_pp<3, T>()>();
   return large ? r : (r > 1 ? r / 2 : 1);
 }
 template <typename T, int R, bool PF>

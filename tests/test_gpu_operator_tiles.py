@@ -1,0 +1,50 @@
+"""Apply and residual restriction of the 3-D operator kernel on one and on two
+LDS tiles (the rule is the tiles' size: Q7 in FP64 takes one), on its z-lines
+straight to memory, against the assembled operator: meshes of 2 cells a
+direction (one patch, every face on the boundary) and of 4 (every patch at an
+interior face in each direction), three right-hand sides."""
+import sys
+
+import numpy as np
+import pytest
+
+from oracle.sipg import kron_operator
+from oracle.transfer import prolongation
+from paper_2405_18982_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2405_18982_amd import dgmg  # noqa: E402
+
+
+@pytest.mark.parametrize("k", [2, 3, 6, 7])
+@pytest.mark.parametrize("bits", [64, 32])
+def test_apply_and_restriction(k, bits):
+    print(f"operator tiles k={k} bits={bits}", flush=True)
+    sys.stdout.flush()
+    dt, u = (torch.float64, 1.1e-16) if bits == 64 else (torch.float32, 6e-8)
+    E = 2 * (k + 1)
+    # three contractions of at most E + 4 terms (unit round-off u); the 1-D
+    # coefficients known to u times the condition of the differentiation, E^4
+    tol = max(1e-12, E ** 4 * u) if bits == 64 else 3 * (E + 4) * u
+    prob = dgmg.Problem(3, k, 1, nrhs_max=3)
+    for level in (0, 1):
+        N = 2 ** (level + 1)
+        A = kron_operator(3, k, N, inputs.sigma_of(k))
+        X, B = (torch.from_numpy(inputs.uniform(s + level, (3, prob.ndofs(level)))).to("cuda", dt) for s in (31, 41))
+        x, b = X.double().cpu().numpy(), B.double().cpu().numpy()
+        got = prob.apply(X, level=level).double().cpu().numpy().reshape(3, -1)
+        for j in range(3):
+            ref = A @ x[j]
+            assert np.linalg.norm(got[j] - ref) <= tol * np.linalg.norm(ref), (level, j)
+        if level:
+            P = prolongation(3, k, N // 2)
+            got = prob.restrict_residual(X, B, level=level).double().cpu().numpy().reshape(3, -1)
+            for j in range(3):
+                ref = P.T @ (b[j] - A @ x[j])
+                assert np.linalg.norm(got[j] - ref) <= tol * np.linalg.norm(ref), j
+    prob.close()
