@@ -3143,6 +3143,18 @@ k_restrict_rf(const Tab<K, T>* __restrict__ t, PatchGrid g, T scale, const T* __
 }
 
 // ------------------------------------------------- prolongation + add
+// Where the sums go.  Bound by memory requests: the lines of the last direction
+// are read ahead of the contractions and written from registers, n (2-D) or
+// n^2 consecutive values a cell, instead of x-rows from the tile after one
+// phase and barrier more.  Measured, lines / rows: FP64 3-D Q7 32^3 42.8 / 56.8 us,
+// Q6 29.8 / 41.3, Q4 12.3 / 15.5, Q3 7.0 / 8.2, 2-D Q5 256^2 8.4 / 10.3; FP32 3-D Q7
+// 22.3 / 24.5, Q3 5.1 / 5.2, 2-D Q7 256^2 7.7 / 8.3.  The rows stay for 3-D Q1 (7.4 /
+// 7.1 us on 64^3) and the FP32 lines of short cells (2-D Q6 9.5 / 7.5, Q3 4.4 / 3.9;
+// 3-D Q2 64^3 14.8 / 13.2): four-byte pieces of runs of 24 bytes or so cost more
+// requests than a row's wide ones.
+template <typename T>
+constexpr bool kProlongLines = sizeof(T) == 8 ? !(D == 3 && K == 1) : (D == 3 ? K >= 3 : K == 7);
+
 template <typename T>
 __device__ __forceinline__ void prolong_body(const PatchGrid& g, const T* __restrict__ xc, T* __restrict__ x,
                                              long long ndof, long long ndof_c, int pid, int lane, T* tile,
@@ -3150,6 +3162,18 @@ __device__ __forceinline__ void prolong_body(const PatchGrid& g, const T* __rest
   const bool active = pid < g.npatch;
   const PatchPos P = patch_pos(g, active ? pid : 0);
   const long long roff = (long long)rhs * ndof;
+  // This lane's line along the last direction, in 3-D with the lanes cell by
+  // cell: n^2 consecutive values a cell.  Its values of x are read ahead of the
+  // contractions, and the last pass adds to them and writes them back.
+  const int ll = (D == 3) ? (lane / (n * n)) % 2 * n + lane % n + E * (lane / (2 * n * n) * n + lane / n % n) : lane;
+  const long long cs = (long long)((D == 3) ? g.N * g.N : g.N) * NC;  // next cell along it
+  constexpr int ns = (D == 3) ? n * n : n;
+  T* xl = x + roff + node_offset(g.N, P, ll % E, ll / E, 0);
+  T xv[E];
+  if (kProlongLines<T> && active) {
+#pragma unroll
+    for (int p = 0; p < E; ++p) xv[p] = xl[(p / n) * cs + (p % n) * ns];
+  }
   // along x: coarse rows (ly, lz) straight from global
   if (active) {
     const int Nc = g.N / 2;
@@ -3171,34 +3195,45 @@ __device__ __forceinline__ void prolong_body(const PatchGrid& g, const T* __rest
     }
   }
   __syncthreads();
-#pragma unroll
-  for (int dir = 1; dir < D; ++dir) {
+  if constexpr (D == 3) {  // along y: lines (px, pz < n)
     if (active) {
-      // lines along dir; coordinates in later directions still < n
-      const int nlines = (D == 3 && dir == 1) ? E * n : E * E;
-      for (int i = lane; i < (D == 2 ? E : nlines); i += TPP) {
-        int base, stride;
-        if (D == 3 && dir == 1) { const int px = i % E, pz = i / E; base = px + pz * SZ; stride = SY; }
-        else line_geom(dir, i, base, stride);
+      for (int i = lane; i < E * n; i += TPP) {
+        const int base = i % E + i / E * SZ;
         T v[n];
 #pragma unroll
-        for (int nu = 0; nu < n; ++nu) v[nu] = tile[base + nu * stride];
+        for (int nu = 0; nu < n; ++nu) v[nu] = tile[base + nu * SY];
 #pragma unroll
         for (int p = 0; p < E; ++p) {
           T s = T(0);
 #pragma unroll
           for (int nu = 0; nu < n; ++nu) s += T(kRef.P[p * n + nu]) * v[nu];
-          tile[base + p * stride] = s;
+          tile[base + p * SY] = s;
         }
       }
     }
     __syncthreads();
   }
   if (active) {
-    for (int i = lane; i < NL; i += TPP) {
-      const int py = i % E, pz = i / E;
+    int base, stride;
+    line_geom(D - 1, ll, base, stride);
+    T v[n];
+#pragma unroll
+    for (int nu = 0; nu < n; ++nu) v[nu] = tile[base + nu * stride];
+#pragma unroll
+    for (int p = 0; p < E; ++p) {
+      T s = T(0);
+#pragma unroll
+      for (int nu = 0; nu < n; ++nu) s += T(kRef.P[p * n + nu]) * v[nu];
+      if constexpr (kProlongLines<T>) xl[(p / n) * cs + (p % n) * ns] = xv[p] + s;
+      else tile[base + p * stride] = s;
+    }
+  }
+  if constexpr (!kProlongLines<T>) {
+    __syncthreads();
+    if (active) {
+      const int py = lane % E, pz = lane / E;
       int base, stride;
-      line_geom(0, i, base, stride);
+      line_geom(0, lane, base, stride);
       const long long row0 = roff + xrow_offset(g.N, P, py, pz);
 #pragma unroll
       for (int a = 0; a < n; ++a) {

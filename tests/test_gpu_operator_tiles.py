@@ -1,6 +1,6 @@
 """Apply and residual restriction of the 3-D operator kernel on one and on two
 LDS tiles (the rule is the tiles' size: Q7 in FP64 takes one), on its z-lines
-straight to memory, against the assembled operator: meshes of 2 cells a
+straight to memory, against the assembled operator, and the prolongation: meshes of 2 cells a
 direction (one patch, every face on the boundary) and of 4 (every patch at an
 interior face in each direction), three right-hand sides."""
 import sys
@@ -47,4 +47,27 @@ def test_apply_and_restriction(k, bits):
             for j in range(3):
                 ref = P.T @ (b[j] - A @ x[j])
                 assert np.linalg.norm(got[j] - ref) <= tol * np.linalg.norm(ref), j
+    prob.close()
+
+
+@pytest.mark.parametrize("dim,k", [(2, 1), (2, 3), (2, 7), (3, 1), (3, 2), (3, 3), (3, 6)])
+@pytest.mark.parametrize("bits", [64, 32])
+def test_prolongation_by_lines_and_by_rows(dim, k, bits):
+    """Both sides of the rule that chooses whether the sums leave by lines of
+    the last direction or by x-rows, one patch and four or eight."""
+    print(f"prolongation d={dim} k={k} bits={bits}", flush=True)
+    dt, u = (torch.float64, 1.1e-16) if bits == 64 else (torch.float32, 6e-8)
+    # dim contractions of n terms, and the weights known to n^4 u
+    tol = max(1e-12, (k + 1) ** 4 * u) if bits == 64 else 3 * (k + 3) * u
+    prob = dgmg.Problem(dim, k, 2, nrhs_max=3)
+    for level in (1, 2):
+        P = prolongation(dim, k, 2 ** level)
+        X = torch.from_numpy(inputs.uniform(51 + level, (3, prob.ndofs(level)))).to("cuda", dt)
+        C = torch.from_numpy(inputs.uniform(61 + level, (3, prob.ndofs(level - 1)))).to("cuda", dt)
+        x, c = X.double().cpu().numpy(), C.double().cpu().numpy()
+        prob.prolongate_add(C, X, level=level)
+        got = X.double().cpu().numpy().reshape(3, -1)
+        for j in range(3):
+            ref = x[j] + P @ c[j]
+            assert np.linalg.norm(got[j] - ref) <= tol * np.linalg.norm(ref), (level, j)
     prob.close()
