@@ -1845,7 +1845,7 @@ k_mass(const Tab<K, T>* __restrict__ t, PatchGrid g, T scale, const T* __restric
 // The Full kernel's operator pass takes the neighbour face data in registers
 // in 3-D, as the apply and the restriction do: on patches within one wave (Q1,
 // Q3) through operator_passes (two tiles of LDS per patch), otherwise through
-// the apply's register-face body (two tiles and four z-face rows); no face
+// the apply's register-face body (kApplyRFPP of LDS per patch); no face
 // arrays either way.
 constexpr bool kFullRF = (D == 3) && kZShfl;
 constexpr bool kFullOnApplyRF = kApplyRF && !kFullRF;
