@@ -58,7 +58,12 @@ constexpr int NL = (D == 2) ? E : E * E;            // lines per direction
 constexpr int NC = (D == 2) ? n * n : n * n * n;    // nodes per cell
 constexpr int NCP = (D == 2) ? 4 : 8;               // cells per patch
 constexpr int SY = E + 1;                           // padded LDS strides
-constexpr int SZ = (D == 3) ? E * SY : 0;
+// 8 more for 8-node cells: with the lanes cell by cell (8 x 8 nodes a wave) x-
+// and y-lines then meet no bank twice, z-lines do; without it all three
+// directions do (Q7 FP64 with / without: smoothing step 32^3 623 / 644 us, 64^3
+// 5.59 / 5.65 ms, apply 64^3 727 / 735 us; FP32 within 1.5%).  No choice of strides
+// brings the other degrees as much.
+constexpr int SZ = (D == 3) ? E * SY + (n == 8 ? 8 : 0) : 0;
 constexpr int TS = (D == 2) ? E * SY : E * SZ;      // padded tile size
 constexpr int NF = (D == 2) ? E : E * E;            // nodes of one patch face
 
