@@ -270,8 +270,8 @@ dgmg_status dgmg_patch_eigen(int degree, double sigma, int smoother_variant, int
 /* Autotuner: for nrhs right-hand sides, time every workgroup shape (patches
  * per workgroup) and patch numbering (plain or XCD-aware) of the FP64
  * apply_sipg on the finest level, and of smooth_patch on every level 1..L in
- * the V-cycle's precision, where the shapes also choose whether a patch
- * fetches its b lines up front (fewer round trips, for latency-bound coarse
+ * the V-cycle's precision, where the shapes also choose, for the smoothers
+ * that form a residual, whether a patch fetches its b lines up front (fewer round trips, for latency-bound coarse
  * levels) or when needed (smaller cache footprint, for the finest level); use
  * the fastest from then on.  Timings run on the CG workspace and the level
  * vectors (their contents are overwritten).  cache_path (may be NULL) names a

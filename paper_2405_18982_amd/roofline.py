@@ -61,7 +61,10 @@ def apply_counts(dim, k, N, nrhs=1, s=8):
 
 
 def smooth_colour_counts(dim, k, N, colour, nrhs=1, s=8):
-    """One colour launch of the smoother on a level with N cells per direction."""
+    """One colour launch of the smoother on a level with N cells per direction,
+    counted as stated: residual of the patch, then the local solve.  The direct
+    form of the Dirichlet kernels reaches the same values with about half of
+    the operations."""
     n = k + 1
     E = 2 * n
     los = patch_los(N, colour, dim)
