@@ -132,33 +132,13 @@ constexpr EOCell make_eo_cell(const double (&B)[n * n]) {
   return r;
 }
 static constexpr EOCell kEOM = make_eo_cell(kRef.M);
-// The same for FP32, each half-sum and half-difference pair on a grid (2^-24 of
-// the next power of two above |A| + |Bo|) on which A + Bo and A - Bo are exact in
-// FP32: the rows of M and the even-odd form then stand for one matrix.
-constexpr EOCell grid_eo_cell(EOCell c) {
-  for (int i = 0; i < kHN * kHN; ++i) {
-    const double m = (c.A[i] < 0 ? -c.A[i] : c.A[i]) + (c.Bo[i] < 0 ? -c.Bo[i] : c.Bo[i]);
-    double q = 1.0;
-    while (q > m) q *= 0.5;
-    q *= 2.0 / 16777216.0;
-    for (double* x : {&c.A[i], &c.Bo[i]}) *x = (double)(long long)(*x / q + (*x < 0 ? -0.5 : 0.5)) * q;
-  }
-  return c;
-}
-static constexpr EOCell kEOMq = grid_eo_cell(kEOM);
 static constexpr EOCell kEOL = make_eo_cell(kRef.Lcons);
 static constexpr EOCell kEOK = make_eo_cell(kRef.Ks);
-
-// The line's mass by even-odd halves; in 2-D FP32 by plain rows, in the very
-// operations that contract the face data (face_dot), where arithmetic does not
-// bound the kernels.
-template <typename T>
-constexpr bool kEOMass = kEOC && !(D == 2 && sizeof(T) == 4);
 
 // bl = B w for the cell c of patch line v (MASS: B = M, else Lcons)
 template <typename T, bool MASS>
 __device__ __forceinline__ void cell_eo(const Line<T>& v, int c, T (&bl)[n]) {
-  constexpr const EOCell& C = !MASS ? kEOL : sizeof(T) == 4 ? kEOMq : kEOM;
+  constexpr const EOCell& C = MASS ? kEOM : kEOL;
   T ve[kHN], vo[kHN];
 #pragma unroll
   for (int j = 0; j < kHN; ++j) {
@@ -190,7 +170,7 @@ __device__ __forceinline__ void cell_eo(const Line<T>& v, int c, T (&bl)[n]) {
 template <typename T>
 __device__ __forceinline__ void line_mass(const Tab<K, T>* __restrict__ t, const Line<T>& v, Line<T>& o,
                                           bool need0 = true, bool needE = true) {
-  if constexpr (kEOMass<T>) {
+  if constexpr (kEOC) {
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
       T bl[n];
@@ -846,23 +826,29 @@ __device__ __forceinline__ void mass_row(int mu, T (&row)[n]) {
   for (int nu = 0; nu < n; ++nu) row[nu] = kMassRows<T>.v[mu * n + nu];
 }
 
-// The mass row that contracts the neighbours' face data: M as the line's own
-// mass has it (line_mass), or the two sides' rounding of M would become a jump
-// that the penalty multiplies.
+// The mass row that contracts the neighbours' face data.  On differences (FP32)
+// it acts as the line's own mass does (line_mass), in the same operations:
+// rounded another way, the two sides' masses would leave a jump that the
+// penalty multiplies.  With the even-odd form (kFaceEO) a row holds its half-sums
+// (n / 2), its half-differences (negative in the mirrored rows) and, for odd n, the
+// coefficient of the middle value, each rounded once: rows and even-odd form on one
+// coarser grid of coefficients instead put the 3-D FP32 operator off by 1.41e-7
+// (Q5), 1.15e-7 (Q6), 1.25e-7 (Q7) on uniform random values, in this form 9.7e-8, 9.5e-8,
+// 9.9e-8.  Elsewhere the plain rows, as mass_row.
+template <typename T>
+constexpr bool kFaceEO = kDiff<T> && kEOC;
 template <typename T>
 constexpr MassRows<T> make_face_rows() {
   MassRows<T> r = make_mass_rows<T>();
-  if (kEOMass<T> && sizeof(T) == 4)
+  if (kFaceEO<T>)
     for (int mu = 0; mu < n; ++mu) {
       const int m = mu < n - 1 - mu ? mu : n - 1 - mu;
+      const bool mid = kOddN && mu == kHN;
       for (int j = 0; j < kHN; ++j) {
-        const bool mid = kOddN && mu == kHN;
-        const double e = mid ? kEOMq.rowm[j] : kEOMq.A[m * kHN + j];
-        const double o = mid ? 0.0 : mu == m ? kEOMq.Bo[m * kHN + j] : -kEOMq.Bo[m * kHN + j];
-        r.v[mu * n + j] = T(e + o);
-        r.v[mu * n + n - 1 - j] = T(e - o);
+        r.v[mu * n + j] = T(mid ? kEOM.rowm[j] : kEOM.A[m * kHN + j]);
+        r.v[mu * n + kHN + j] = T(mid ? 0.0 : mu == m ? kEOM.Bo[m * kHN + j] : -kEOM.Bo[m * kHN + j]);
       }
-      if (kOddN) r.v[mu * n + kHN] = T(mu == kHN ? kEOMq.rowm[kHN] : kEOMq.colm[m]);
+      if (kOddN) r.v[mu * n + n - 1] = T(mid ? kEOM.rowm[kHN] : kEOM.colm[m]);
     }
   return r;
 }
@@ -877,6 +863,17 @@ __device__ __forceinline__ void face_row(int mu, T (&row)[n]) {
 template <typename T, typename W>
 __device__ __forceinline__ T face_dot(const T (&row)[n], W w) {
   T s = T(0);
+  if constexpr (kFaceEO<T>) {
+    T v[n], d = T(0);
+#pragma unroll
+    for (int nu = 0; nu < n; ++nu) v[nu] = w(nu);
+#pragma unroll
+    for (int j = 0; j < kHN; ++j) s += row[j] * (v[j] + v[n - 1 - j]);
+    if constexpr (kOddN) s += row[n - 1] * v[kHN];
+#pragma unroll
+    for (int j = 0; j < kHN; ++j) d += row[kHN + j] * (v[j] - v[n - 1 - j]);
+    return s + d;
+  }
 #pragma unroll
   for (int nu = 0; nu < n; ++nu) s += row[nu] * w(nu);
   return s;
