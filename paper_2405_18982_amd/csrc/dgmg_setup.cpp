@@ -41,10 +41,11 @@ bool cholesky(const std::vector<Real>& A, int m, std::vector<Real>& C) {
 }
 
 // Cyclic Jacobi rotations on the symmetric matrix A until its off-diagonal part
-// is below eps of it (in the squared norm), gathered in Q (in: an orthogonal
-// matrix): on return A ~ diag(w).
+// is below eps of it (in the squared norm) or shrinks no further, gathered in Q
+// (in: an orthogonal matrix): on return A ~ diag(w).
 template <typename R>
 void jacobi_rotate(std::vector<R>& A, int m, R eps, std::vector<R>& Q) {
+  R last = std::numeric_limits<R>::infinity();
   for (int sweep = 0; sweep < 100; ++sweep) {
     R off = 0, tot = 0;
     for (int i = 0; i < m; ++i)
@@ -52,7 +53,8 @@ void jacobi_rotate(std::vector<R>& A, int m, R eps, std::vector<R>& Q) {
         tot += A[i * m + j] * A[i * m + j];
         if (i != j) off += A[i * m + j] * A[i * m + j];
       }
-    if (off <= eps * tot) break;
+    if (off <= eps * tot || !(off < last)) break;
+    last = off;
     for (int p = 0; p < m; ++p)
       for (int q = p + 1; q < m; ++q) {
         const R apq = A[p * m + q];
@@ -86,7 +88,7 @@ void jacobi_rotate(std::vector<R>& A, int m, R eps, std::vector<R>& Q) {
 void jacobi_eigen(const std::vector<Real>& A, int m, std::vector<Real>& w, std::vector<Real>& Q) {
   std::vector<double> Ad(A.begin(), A.end()), Qd(m * m, 0.0);
   for (int i = 0; i < m; ++i) Qd[i * m + i] = 1.0;
-  jacobi_rotate<double>(Ad, m, 1e-32, Qd);
+  jacobi_rotate<double>(Ad, m, 1e-26, Qd);
   Q.assign(Qd.begin(), Qd.end());
   for (int j = 0; j < m; ++j) {  // modified Gram-Schmidt on the columns
     for (int l = 0; l <= j; ++l) {
@@ -111,7 +113,7 @@ void jacobi_eigen(const std::vector<Real>& A, int m, std::vector<Real>& w, std::
       for (int l = 0; l < m; ++l) s += Q[l * m + i] * AQ[l * m + j];
       B[i * m + j] = B[j * m + i] = s;
     }
-  jacobi_rotate<Real>(B, m, 1e-37L, Q);
+  jacobi_rotate<Real>(B, m, 1e-36L, Q);
   w.resize(m);
   for (int i = 0; i < m; ++i) w[i] = B[i * m + i];
 }
@@ -124,17 +126,20 @@ void jacobi_eigen(const std::vector<Real>& A, int m, std::vector<Real>& w, std::
 bool basis_eigenpairs(const std::vector<Real>& L, const std::vector<Real>& Mp, int E,
                       const std::vector<Real>& Cb, int m, std::vector<double>& Sout,
                       std::vector<double>& lamout, const char** err) {
-  std::vector<Real> Lt(m * m, 0.0), Mt(m * m, 0.0);
+  std::vector<Real> Lt(m * m), Mt(m * m), LC(E * m, 0), MC(E * m, 0);
+  for (int p = 0; p < E; ++p)
+    for (int q = 0; q < E; ++q)
+      for (int j = 0; j < m; ++j) {
+        LC[p * m + j] += L[p * E + q] * Cb[q * m + j];
+        MC[p * m + j] += Mp[p * E + q] * Cb[q * m + j];
+      }
   for (int i = 0; i < m; ++i)
     for (int j = 0; j < m; ++j) {
-      Real sl = 0.0, sm = 0.0;
-      for (int p = 0; p < E; ++p)
-        for (int q = 0; q < E; ++q) {
-          const Real w = Cb[p * m + i] * Cb[q * m + j];
-          if (w == 0.0) continue;
-          sl += w * L[p * E + q];
-          sm += w * Mp[p * E + q];
-        }
+      Real sl = 0, sm = 0;
+      for (int p = 0; p < E; ++p) {
+        sl += Cb[p * m + i] * LC[p * m + j];
+        sm += Cb[p * m + i] * MC[p * m + j];
+      }
       Lt[i * m + j] = sl;
       Mt[i * m + j] = sm;
     }
