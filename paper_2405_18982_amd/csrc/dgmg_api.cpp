@@ -386,9 +386,12 @@ dgmg_status ensure_alt(dgmg_ctx* c);
 // (pre-smoothing in the V-cycle); colour 0 then takes r = b and writes every
 // node, so x need not be cleared first.
 // alt: the second copy of x for the Full smoother (nullptr: the level's own).
+// callers_x: x is the caller's and may hold NaNs or infinities, which must spread
+// (PatchGrid::guard).  In a V-cycle they come from b alone: pre-smoothing spreads
+// them over the patches and the coarse correction over every entry.
 template <typename T>
 dgmg_status op_smooth(dgmg_ctx* c, int l, T* x, const T* b, int reverse, int nrhs,
-                      bool from_zero = false, T* alt = nullptr) {
+                      bool from_zero = false, T* alt = nullptr, bool callers_x = false) {
   const double sc = level_scale(c, l);
   const int nc = 1 << c->dim;
   const bool full = c->variant == DGMG_SMOOTH_FULL;
@@ -409,6 +412,7 @@ dgmg_status op_smooth(dgmg_ctx* c, int l, T* x, const T* b, int reverse, int nrh
     g.xcd_remap = xcd_remap_flag(tu.remap);
     T* out = full ? other : cur;
     const int zero = (from_zero && !reverse && i == 0) ? 1 : 0;
+    g.guard = !callers_x ? 0 : i == 0 ? 2 : reverse ? 1 : 0;
     HIPCHK(c, kset<T>(c).smooth[tu.shape](tab_of<T>(c), g, (T)sc, (T)(1.0 / sc), c->variant, zero,
                                           cur, out, b, nrhs, c->lv[l].ndof, c->stream));
     if (full) {
@@ -918,14 +922,14 @@ DGMG_API dgmg_status dgmg_smooth_patch(dgmg_ctx* c, int level, double* x, const 
                                        int reverse_colours, int nrhs) {
   RET(check_level(c, level, 1, nrhs));
   if (!x || !b) return fail(c, DGMG_ERR_ARG, "null vector");
-  return op_smooth<double>(c, level, x, b, reverse_colours, nrhs);
+  return op_smooth<double>(c, level, x, b, reverse_colours, nrhs, false, nullptr, true);
 }
 
 DGMG_API dgmg_status dgmg_smooth_patch_f32(dgmg_ctx* c, int level, float* x, const float* b,
                                            int reverse_colours, int nrhs) {
   RET(check_level(c, level, 1, nrhs));
   if (!x || !b) return fail(c, DGMG_ERR_ARG, "null vector");
-  return op_smooth<float>(c, level, x, b, reverse_colours, nrhs);
+  return op_smooth<float>(c, level, x, b, reverse_colours, nrhs, false, nullptr, true);
 }
 
 DGMG_API dgmg_status dgmg_restrict_residual(dgmg_ctx* c, int level, const double* x,

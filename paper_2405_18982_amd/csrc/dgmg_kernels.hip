@@ -2113,13 +2113,14 @@ __device__ __forceinline__ T& at32(T* p, unsigned o) {
 // paper's residual) differs only in the outer trace, for which it takes the
 // patch's own end value.  ZERO: x = 0 on entry, so there are no faces, and
 // every node of the tile is written.  INT: the patch is an interior one.
+// GUARD: the launch has patches that look at their old values, this one if guard.
 //
 // Order of the loads: the face layers and lines, then (where the registers
 // allow it) b, all before the first of them is used -- one memory round trip.
-template <typename T, int MODE, bool ZERO, bool INT>
+template <typename T, int MODE, bool ZERO, bool INT, bool GUARD>
 __device__ __forceinline__ void gs_body(const Tab<K, T>* __restrict__ t, int N, const PatchPos& P, T scale,
                                         T inv_scale, T* __restrict__ xr, const T* __restrict__ br, bool active,
-                                        int lane, T* A) {
+                                        int lane, T* A, bool guard) {
   static_assert(NL == TPP && NF == TPP, "one line and one face node per lane");
   using L1 = GsLine<T, INT>;
   const int tyx = INT ? 0 : P.ty[0], tyy = INT ? 0 : P.ty[1], tyl = INT ? 0 : P.ty[D - 1];
@@ -2155,6 +2156,10 @@ __device__ __forceinline__ void gs_body(const Tab<K, T>* __restrict__ t, int N, 
 #pragma unroll
     for (int p = 0; p < E; ++p) bl.v[p] = at32(p < n ? b0 : b1, lo + (p % n) * ln);
   };
+  // The new values do not depend on the old ones on V, yet a NaN or an infinity
+  // among these must not vanish: nonf, 0 or NaN, joins the lane's load line, and the
+  // contractions carry it over the patch, as those of a residual do.
+  T nonf = T(0);
   // faces of the last direction (Fl, Ul; Wl nodal) and of the x-direction (F is
   // scale W), and in 3-D of the y-direction (Wy in the eigenbasis along z)
   FacePair<T> Fl{}, Ul{}, Wl{}, Ux{}, Wx{}, Fy{}, Uy{}, Wy{};
@@ -2184,6 +2189,11 @@ __device__ __forceinline__ void gs_body(const Tab<K, T>* __restrict__ t, int N, 
     // patch's own node; its value is not used)
     const bool ownl = MODE == 2 || (tyl & 1), ownr = MODE == 2 || (tyl & 2);
     T raw[4] = {T(0), T(0), T(0), T(0)};
+    Line<T> old{};
+    if (GUARD && active && guard) {
+#pragma unroll
+      for (int p = 0; p < E; ++p) old.v[p] = at32(p < n ? x0 : x1, lo + (p % n) * ln);
+    }
     if (active) {
       raw[0] = at32(x0, lo);
       raw[1] = ownl ? raw[0] : at32(x0 - lc, lo + K * ln);
@@ -2225,6 +2235,10 @@ __device__ __forceinline__ void gs_body(const Tab<K, T>* __restrict__ t, int N, 
         }
 #pragma unroll
         for (int f = 0; f < 4; ++f) A[(8 + f) * SZ + q * SY + a] = raw[f];
+        if (GUARD && guard) {
+#pragma unroll
+          for (int p = 0; p < E; ++p) nonf += T(0) * old.v[p];
+        }
       }
       __syncthreads();
       // M_x on the z-layers (planes 8..11 -> 12..15) and on the y-faces (this
@@ -2307,6 +2321,10 @@ __device__ __forceinline__ void gs_body(const Tab<K, T>* __restrict__ t, int N, 
         A[7 * E + a] = u3;
 #pragma unroll
         for (int f = 0; f < 4; ++f) A[f * E + a] = raw[f];
+        if (GUARD && guard) {
+#pragma unroll
+          for (int p = 0; p < E; ++p) nonf += T(0) * old.v[p];
+        }
       }
       __syncthreads();
       if (active) {
@@ -2342,6 +2360,7 @@ __device__ __forceinline__ void gs_body(const Tab<K, T>* __restrict__ t, int N, 
   // last direction: S^T b - its faces
   if (active) {
     Line<T> o;
+    if constexpr (GUARD) bl.v[n] += nonf;  // node n is in every V
     L1::fwd(t, tyl, bl, Fl, Ul, o);
     store_line(A, bz, sl, o);
   }
@@ -2394,7 +2413,7 @@ __device__ __forceinline__ void gs_body(const Tab<K, T>* __restrict__ t, int N, 
 // this (barriers inside), with pid >= g.npatch for idle slots.
 // UNI: no wave holds lanes of patches of different types (the barriers of the
 // two paths it then may take are the same in number).
-template <typename T, int MODE, bool PREFETCH, bool ZERO, bool UNI = (TPP % 64 == 0)>
+template <typename T, int MODE, bool PREFETCH, bool ZERO, bool UNI = (TPP % 64 == 0), bool GUARD = false>
 __device__ __forceinline__ void smooth_body(const Tab<K, T>* __restrict__ t, const PatchGrid& g, T scale,
                                             T inv_scale, const T* __restrict__ xin, T* __restrict__ xout,
                                             const T* __restrict__ b, long long ndof, int pid, int lane,
@@ -2407,9 +2426,9 @@ __device__ __forceinline__ void smooth_body(const Tab<K, T>* __restrict__ t, con
     T* xv = xout + (long long)rhs * ndof;
     const T* bv = b + (long long)rhs * ndof;
     if (UNI && (Q.ty[0] | Q.ty[1] | Q.ty[2]) == 0)
-      gs_body<T, MODE, ZERO, true>(t, g.N, Q, scale, inv_scale, xv, bv, act, lane, sm);
+      gs_body<T, MODE, ZERO, true, GUARD>(t, g.N, Q, scale, inv_scale, xv, bv, act, lane, sm, g.guard == 2);
     else
-      gs_body<T, MODE, ZERO, false>(t, g.N, Q, scale, inv_scale, xv, bv, act, lane, sm);
+      gs_body<T, MODE, ZERO, false, GUARD>(t, g.N, Q, scale, inv_scale, xv, bv, act, lane, sm, true);
   } else {
   constexpr bool FULL = (MODE == 3);
   constexpr int SP = FULL ? SP_FULL : (MODE == 4) ? SP_CLAMPED : SP_DIR;
@@ -2603,7 +2622,7 @@ constexpr int smooth_waves() {
   if (sizeof(T) == 8) return K <= 4 ? 4 : 2;
   return K <= 3 ? 8 : K == 4 ? 6 : K == 6 ? 4 : 5;
 }
-template <typename T, int PPB, int MODE, bool PREFETCH, bool ZERO = false, bool RP = false>
+template <typename T, int PPB, int MODE, bool PREFETCH, bool ZERO = false, bool RP = false, bool GUARD = false>
 __global__ void __launch_bounds__(TPP * PPB, (smooth_waves<T, MODE, TPP * PPB>()))
 k_smooth(const Tab<K, T>* __restrict__ t, PatchGrid g, T scale, T inv_scale,
          const T* __restrict__ xin, T* __restrict__ xout, const T* __restrict__ b, long long ndof) {
@@ -2614,8 +2633,8 @@ k_smooth(const Tab<K, T>* __restrict__ t, PatchGrid g, T scale, T inv_scale,
   slot_work<PPB, RP>(g, slot, pid, rhs);
   // one patch per workgroup, or one patch for all its slots
   constexpr bool UNI = PPB == 1 || RP || TPP % 64 == 0;
-  smooth_body<T, MODE, PREFETCH, ZERO, UNI>(t, g, scale, inv_scale, xin, xout, b, ndof, pid, lane,
-                                            smem + slot * PP, rhs);
+  smooth_body<T, MODE, PREFETCH, ZERO, UNI, GUARD>(t, g, scale, inv_scale, xin, xout, b, ndof, pid, lane,
+                                                   smem + slot * PP, rhs);
 }
 
 
@@ -3632,9 +3651,15 @@ hipError_t launch_smooth_rpack(const Tab<K, T>* tb, PatchGrid g, T scale, T inv_
   else if (variant == 3)
     hipLaunchKernelGGL((k_smooth<T, R, 4, PF, false, true>), grid, block, 0, s, tb, g, scale, inv_scale,
                        xout, xout, b, ndof);
+  else if (variant == 1 && kDirect<1> && g.guard)
+    hipLaunchKernelGGL((k_smooth<T, R, 2, PFD, false, true, kDirect<1>>), grid, block, 0, s, tb, g, scale,
+                       inv_scale, xout, xout, b, ndof);
   else if (variant == 1)
     hipLaunchKernelGGL((k_smooth<T, R, 2, PFD, false, true>), grid, block, 0, s, tb, g, scale, inv_scale,
                        xout, xout, b, ndof);
+  else if (kDirect<1> && g.guard)
+    hipLaunchKernelGGL((k_smooth<T, R, 1, PFD, false, true, kDirect<1>>), grid, block, 0, s, tb, g, scale,
+                       inv_scale, xout, xout, b, ndof);
   else
     hipLaunchKernelGGL((k_smooth<T, R, 1, PFD, false, true>), grid, block, 0, s, tb, g, scale, inv_scale,
                        xout, xout, b, ndof);
@@ -3687,9 +3712,15 @@ hipError_t launch_smooth(const void* tab, PatchGrid g, T scale, T inv_scale, int
   else if (variant == 3)
     hipLaunchKernelGGL((k_smooth<T, PPB, 4, PF>), grid, dim3(TPP * PPB), 0, s, tb, g, scale,
                        inv_scale, xout, xout, b, ndof);
+  else if (variant == 1 && kDirect<1> && g.guard)
+    hipLaunchKernelGGL((k_smooth<T, PPB, 2, PFD, false, false, kDirect<1>>), grid, dim3(TPP * PPB), 0, s, tb, g,
+                       scale, inv_scale, xout, xout, b, ndof);
   else if (variant == 1)
     hipLaunchKernelGGL((k_smooth<T, PPB, 2, PFD>), grid, dim3(TPP * PPB), 0, s, tb, g, scale,
                        inv_scale, xout, xout, b, ndof);
+  else if (kDirect<1> && g.guard)
+    hipLaunchKernelGGL((k_smooth<T, PPB, 1, PFD, false, false, kDirect<1>>), grid, dim3(TPP * PPB), 0, s, tb, g,
+                       scale, inv_scale, xout, xout, b, ndof);
   else
     hipLaunchKernelGGL((k_smooth<T, PPB, 1, PFD>), grid, dim3(TPP * PPB), 0, s, tb, g, scale,
                        inv_scale, xout, xout, b, ndof);
