@@ -271,14 +271,18 @@ dgmg_status dgmg_patch_eigen(int degree, double sigma, int smoother_variant, int
  * per workgroup) and patch numbering (plain or XCD-aware) of the FP64
  * apply_sipg on the finest level, and of smooth_patch on every level 1..L in
  * the V-cycle's precision, where the shapes also choose, for the smoothers
- * that form a residual, whether a patch fetches its b lines up front (fewer round trips, for latency-bound coarse
- * levels) or when needed (smaller cache footprint, for the finest level); use
- * the fastest from then on.  Timings run on the CG workspace and the level
- * vectors (their contents are overwritten).  cache_path (may be NULL) names a
- * JSON file of earlier results keyed by architecture, dim, degree, levels,
- * nrhs, precision, kernel and level; cached entries are used without timing
- * and new ones added.  report (may be NULL): host buffer receiving one line
- * per decision.  Drops captured V-cycle graphs. */
+ * that form a residual, whether a patch fetches its b lines up front (fewer
+ * round trips, for latency-bound coarse levels) or when needed (smaller cache
+ * footprint, for the finest level); use the fastest from then on.  Timings run
+ * on the CG workspace and the level vectors (their contents are overwritten).
+ * cache_path (may be NULL) names a JSON file of earlier results keyed by
+ * architecture, dim, degree, levels, nrhs, precision, kernel and level;
+ * cached entries are used without timing and new ones added.  New smoother
+ * entries name the smoother variant they were timed with and hold for it
+ * alone, and all name a revision of the kernels, outside which they are timed
+ * again; entries that name neither hold for every variant without one of its own.
+ * report (may be NULL): host buffer receiving one line per decision.  Drops
+ * captured V-cycle graphs. */
 dgmg_status dgmg_autotune(dgmg_ctx* ctx, int nrhs, const char* cache_path, char* report,
                           int report_len);
 

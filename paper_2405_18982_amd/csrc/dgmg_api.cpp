@@ -6,6 +6,7 @@
 //   level l = L .. 1: smooth (2^d colour launches), residual + restriction
 //   level 0:          exact coarse solve
 //   level l = 1 .. L: prolongation + add, smooth (colours reversed)
+#include <algorithm>
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -1331,7 +1332,11 @@ namespace {
 // Times every workgroup shape x XCD numbering of apply and smooth on the
 // finest level with HIP events (best of three batches) and keeps the fastest.
 // Results are cached in a JSON object, one entry per line:
-//   "gfx950/d3/k3/L4/nrhs16/fp64/smooth": {"shape": 0, "remap": 1, "us": 16.50},
+//   "gfx950/d3/k3/L4/nrhs16/fp64/smooth/l4/v0": {"shape": 0, "remap": 1, "us": 16.50, "rev": 1},
+// v0: the smoother variant the entry was timed with (none for the apply, which all
+// share); rev: kTuneRev of the library that timed it, outside which it is timed
+// again.  Entries without both (written by hand, or before there were any) hold for
+// every variant that has none of its own.
 
 std::string tune_key(const dgmg_ctx* c, int nrhs, int prec, const char* kernel) {
   char buf[128];
@@ -1340,11 +1345,23 @@ std::string tune_key(const dgmg_ctx* c, int nrhs, int prec, const char* kernel) 
   return buf;
 }
 
+// Raised whenever a shape comes to mean another kernel, so that timings of the
+// former one are not kept.
+constexpr int kTuneRev = 1;
+
 struct CacheEntry {
   std::string key;
   int shape, remap;
   double us;
+  int rev;  // -1: not given
 };
+
+// the integer after "name": in a cache line, or -1
+int cache_field(const char* line, const char* name) {
+  const char* p = std::strstr(line, name);
+  int v;
+  return p && std::sscanf(p + std::strlen(name), "\": %d", &v) == 1 ? v : -1;
+}
 
 std::vector<CacheEntry> read_cache(const char* path) {
   std::vector<CacheEntry> out;
@@ -1358,6 +1375,7 @@ std::vector<CacheEntry> read_cache(const char* path) {
     if (std::sscanf(line, " \"%255[^\"]\": {\"shape\": %d, \"remap\": %d, \"us\": %lf", key, &e.shape,
                     &e.remap, &e.us) == 4) {
       e.key = key;
+      e.rev = cache_field(line, "\"rev");
       out.push_back(e);
     }
   }
@@ -1371,9 +1389,12 @@ void write_cache(const char* path, const std::vector<CacheEntry>& es) {
   FILE* f = std::fopen(tmp.c_str(), "w");
   if (!f) return;
   std::fprintf(f, "{\n");
-  for (size_t i = 0; i < es.size(); ++i)
-    std::fprintf(f, "  \"%s\": {\"shape\": %d, \"remap\": %d, \"us\": %.3f}%s\n", es[i].key.c_str(),
-                 es[i].shape, es[i].remap, es[i].us, i + 1 < es.size() ? "," : "");
+  for (size_t i = 0; i < es.size(); ++i) {
+    std::fprintf(f, "  \"%s\": {\"shape\": %d, \"remap\": %d, \"us\": %.3f", es[i].key.c_str(), es[i].shape,
+                 es[i].remap, es[i].us);
+    if (es[i].rev >= 0) std::fprintf(f, ", \"rev\": %d", es[i].rev);
+    std::fprintf(f, "}%s\n", i + 1 < es.size() ? "," : "");
+  }
   std::fprintf(f, "}\n");
   std::fclose(f);
   std::rename(tmp.c_str(), path);
@@ -1460,14 +1481,17 @@ DGMG_API dgmg_status dgmg_autotune(dgmg_ctx* c, int nrhs, const char* cache_path
     const int pi = jb.prec == 64 ? 0 : 1;
     dgmg_ctx::Tuning& slot = jb.smooth ? c->tune_smooth[pi][jb.level] : c->tune_apply[pi];
     const int nshapes = jb.smooth ? dgmg::kSmoothShapes : dgmg::kApplyShapes;
+    const std::string own = jb.smooth ? key + "/v" + std::to_string((int)c->variant) : key;
     bool found = false;
-    for (const CacheEntry& e : cache)
-      if (e.key == key && e.shape >= 0 && e.shape < nshapes && (e.remap == 0 || e.remap == 1)) {
-        slot.shape = e.shape;
-        slot.remap = e.remap;
-        slot.us = e.us;
-        found = true;
-      }
+    for (const std::string& k : {key, own})  // the latter goes before the former
+      for (const CacheEntry& e : cache)
+        if (e.key == k && e.shape >= 0 && e.shape < nshapes && (e.remap == 0 || e.remap == 1) &&
+            (e.rev < 0 || e.rev == kTuneRev)) {
+          slot.shape = e.shape;
+          slot.remap = e.remap;
+          slot.us = e.us;
+          found = true;
+        }
     if (!found) {
       Level& Lv = c->lv[jb.level];
       const long long n = Lv.ndof * nrhs;
@@ -1482,7 +1506,10 @@ DGMG_API dgmg_status dgmg_autotune(dgmg_ctx* c, int nrhs, const char* cache_path
         RET(zero_vec<float>(c, Lv.b32, n));
         RET(tune_kernel<float>(c, nrhs, jb.smooth, jb.level, Lv.x32, Lv.b32, slot));
       }
-      cache.push_back({key, slot.shape, slot.remap, slot.us});
+      // (an outdated entry of this job makes room)
+      cache.erase(std::remove_if(cache.begin(), cache.end(), [&](const CacheEntry& e) { return e.key == own; }),
+                  cache.end());
+      cache.push_back({own, slot.shape, slot.remap, slot.us, kTuneRev});
       dirty = true;
     }
     char line[256];
