@@ -1406,7 +1406,7 @@ dgmg_status tune_kernel(dgmg_ctx* c, int nrhs, bool smooth, int level, T* x, T* 
   // candidate shapes; those that would repeat another are left out
   std::vector<int> shapes;
   const KernelSet<T>& ks = kset<T>(c);
-  const bool rpack = nrhs > 1 && (smooth ? ks.smooth_rpack : ks.apply_rpack);
+  const bool rpack = nrhs > 1 && (smooth ? ks.smooth_rpack[c->variant] > 1 : ks.apply_rpack != 0);
   if (smooth) {
     const bool hi = c->variant == DGMG_SMOOTH_CLAMPED ? ks.smooth_split : ks.smooth_hi_full;
     const bool direct = ks.smooth_direct && (c->variant == DGMG_SMOOTH_EXACT || c->variant == DGMG_SMOOTH_LOCAL);

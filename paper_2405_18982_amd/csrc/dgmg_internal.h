@@ -115,10 +115,10 @@ struct KernelSet {
                          long long ndof, hipStream_t s);
   // 1 where apply shape 2 (face data in registers) differs from shape 0
   int apply_rf;
-  // 1 where the right-hand-side-packed shapes (apply 3, smoother 8..11) hold
-  // more than one slot per workgroup
+  // 1 where the right-hand-side-packed apply (shape 3) holds more than one slot
+  // per workgroup; slots of the packed smoother (shapes 9, 11) by variant
   int apply_rpack;
-  int smooth_rpack;
+  int smooth_rpack[4];
   hipError_t (*mass)(const void* tab, PatchGrid g, T scale, const T* x, T* y, int nrhs,
                      long long ndof, hipStream_t s);
   // variant: DGMG_SMOOTH_* of the context.  The Dirichlet kernels update x in

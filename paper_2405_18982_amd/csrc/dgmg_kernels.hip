@@ -2622,11 +2622,14 @@ constexpr int smooth_waves() {
   if (sizeof(T) == 8) return K <= 4 ? 4 : 2;
   return K <= 3 ? 8 : K == 4 ? 6 : K == 6 ? 4 : 5;
 }
+// LDS a workgroup of several right-hand sides may take: half a CU's
+constexpr int kPackedLDS = 80 * 1024;
 template <typename T, int PPB, int MODE, bool PREFETCH, bool ZERO = false, bool RP = false, bool GUARD = false>
 __global__ void __launch_bounds__(TPP * PPB, (smooth_waves<T, MODE, TPP * PPB>()))
 k_smooth(const Tab<K, T>* __restrict__ t, PatchGrid g, T scale, T inv_scale,
          const T* __restrict__ xin, T* __restrict__ xout, const T* __restrict__ b, long long ndof) {
   constexpr int PP = smooth_pp<MODE, T>();
+  static_assert(!RP || PPB * PP * (int)sizeof(T) <= kPackedLDS, "right-hand sides packed for this variant's footprint");
   __shared__ T smem[PPB * PP];
   const int slot = slot_of(), lane = threadIdx.x % TPP;
   int pid, rhs;
@@ -3550,7 +3553,7 @@ struct Shape {
 template <typename T, int PP>
 constexpr int rpack_slots() {
   int r = (D == 3) ? 8 : 16;
-  while (r > 1 && (TPP * r > 1024 || r * PP * (int)sizeof(T) > 80 * 1024)) r /= 2;
+  while (r > 1 && (TPP * r > 1024 || r * PP * (int)sizeof(T) > kPackedLDS)) r /= 2;
   return r;
 }
 template <typename T>
@@ -3618,51 +3621,28 @@ hipError_t launch_mass(const void* tab, PatchGrid g, T scale, const T* x, T* y, 
 // the paper's residual / Full / clamped
 constexpr bool kOnePatchShape = !kSplitOK && PPB_DEFAULT > 1;
 // shapes 8..11 (bit 3): one patch for several right-hand sides per workgroup,
-// bit 0 selecting the larger slot count, bit 1 the prefetch of b
-template <typename T>
+// bit 0 selecting the larger slot count (by the variant's own LDS footprint),
+// bit 1 the prefetch of b
+template <typename T, int MODE>
 constexpr int rpack_smooth_slots(bool large) {
-  constexpr int r = rpack_slots<T, smooth_pp<3, T>()>();
+  constexpr int r = rpack_slots<T, smooth_pp<MODE, T>()>();
   return large ? r : (r > 1 ? r / 2 : 1);
 }
-template <typename T, int R, bool PF>
-hipError_t launch_smooth_rpack(const Tab<K, T>* tb, PatchGrid g, T scale, T inv_scale, int variant,
-                               int zero, const T* xin, T* xout, const T* b, int nrhs, long long ndof,
-                               hipStream_t s) {
-  constexpr bool PFD = PF && !kDirect<1>;
+template <typename T, int MODE, bool LARGE, bool PF>
+hipError_t launch_smooth_rpack(const Tab<K, T>* tb, PatchGrid g, T scale, T inv_scale, int zero, const T* xin,
+                               T* xout, const T* b, int nrhs, long long ndof, hipStream_t s) {
+  constexpr int R = rpack_smooth_slots<T, MODE>(LARGE);
+  constexpr bool PFD = PF && !kDirect<MODE>;
   const dim3 grid(g.npatch, (nrhs + R - 1) / R), block(TPP * R);
-  if (zero) {
-    if (variant == 2)
-      hipLaunchKernelGGL((k_smooth<T, R, 3, false, true, true>), grid, block, 0, s, tb, g, scale,
-                         inv_scale, xin, xout, b, ndof);
-    else if (variant == 3)
-      hipLaunchKernelGGL((k_smooth<T, R, 4, false, true, true>), grid, block, 0, s, tb, g, scale,
-                         inv_scale, xout, xout, b, ndof);
-    else if (variant == 1)
-      hipLaunchKernelGGL((k_smooth<T, R, 2, false, true, true>), grid, block, 0, s, tb, g, scale,
-                         inv_scale, xout, xout, b, ndof);
-    else
-      hipLaunchKernelGGL((k_smooth<T, R, 1, false, true, true>), grid, block, 0, s, tb, g, scale,
-                         inv_scale, xout, xout, b, ndof);
-    return hipGetLastError();
-  }
-  if (variant == 2)
-    hipLaunchKernelGGL((k_smooth<T, R, 3, PF, false, true>), grid, block, 0, s, tb, g, scale, inv_scale,
-                       xin, xout, b, ndof);
-  else if (variant == 3)
-    hipLaunchKernelGGL((k_smooth<T, R, 4, PF, false, true>), grid, block, 0, s, tb, g, scale, inv_scale,
-                       xout, xout, b, ndof);
-  else if (variant == 1 && kDirect<1> && g.guard)
-    hipLaunchKernelGGL((k_smooth<T, R, 2, PFD, false, true, kDirect<1>>), grid, block, 0, s, tb, g, scale,
-                       inv_scale, xout, xout, b, ndof);
-  else if (variant == 1)
-    hipLaunchKernelGGL((k_smooth<T, R, 2, PFD, false, true>), grid, block, 0, s, tb, g, scale, inv_scale,
-                       xout, xout, b, ndof);
-  else if (kDirect<1> && g.guard)
-    hipLaunchKernelGGL((k_smooth<T, R, 1, PFD, false, true, kDirect<1>>), grid, block, 0, s, tb, g, scale,
-                       inv_scale, xout, xout, b, ndof);
+  if (zero)
+    hipLaunchKernelGGL((k_smooth<T, R, MODE, false, true, true>), grid, block, 0, s, tb, g, scale, inv_scale, xin,
+                       xout, b, ndof);
+  else if (kDirect<MODE> && g.guard)
+    hipLaunchKernelGGL((k_smooth<T, R, MODE, PFD, false, true, kDirect<MODE>>), grid, block, 0, s, tb, g, scale,
+                       inv_scale, xin, xout, b, ndof);
   else
-    hipLaunchKernelGGL((k_smooth<T, R, 1, PFD, false, true>), grid, block, 0, s, tb, g, scale, inv_scale,
-                       xout, xout, b, ndof);
+    hipLaunchKernelGGL((k_smooth<T, R, MODE, PFD, false, true>), grid, block, 0, s, tb, g, scale, inv_scale, xin,
+                       xout, b, ndof);
   return hipGetLastError();
 }
 template <typename T, int V>
@@ -3674,9 +3654,14 @@ hipError_t launch_smooth(const void* tab, PatchGrid g, T scale, T inv_scale, int
   g.nrhs = nrhs;
   const Tab<K, T>* tb = (const Tab<K, T>*)tab;
   if constexpr ((V & 8) != 0) {
-    constexpr int R = rpack_smooth_slots<T>((V & 1) != 0);
-    return launch_smooth_rpack<T, R, PF>(tb, g, scale, inv_scale, variant, zero, xin, xout, b, nrhs, ndof,
-                                         s);
+    constexpr bool LG = (V & 1) != 0;
+    if (variant == 2)
+      return launch_smooth_rpack<T, 3, LG, PF>(tb, g, scale, inv_scale, zero, xin, xout, b, nrhs, ndof, s);
+    if (variant == 3)
+      return launch_smooth_rpack<T, 4, LG, PF>(tb, g, scale, inv_scale, zero, xout, xout, b, nrhs, ndof, s);
+    if (variant == 1)
+      return launch_smooth_rpack<T, 2, LG, PF>(tb, g, scale, inv_scale, zero, xout, xout, b, nrhs, ndof, s);
+    return launch_smooth_rpack<T, 1, LG, PF>(tb, g, scale, inv_scale, zero, xout, xout, b, nrhs, ndof, s);
   }
   dim3 grid((g.npatch + PPB - 1) / PPB, nrhs);
   if constexpr (SPLIT) {
@@ -3818,7 +3803,10 @@ KernelSet<T> make_set() {
   k.apply[3] = &launch_apply_rpack<T>;
   k.apply_rf = kApplyRF ? 1 : 0;
   k.apply_rpack = rpack_apply_slots<T>() > 1 ? 1 : 0;
-  k.smooth_rpack = rpack_smooth_slots<T>(true) > 1 ? 1 : 0;
+  k.smooth_rpack[0] = rpack_smooth_slots<T, 1>(true);
+  k.smooth_rpack[1] = rpack_smooth_slots<T, 2>(true);
+  k.smooth_rpack[2] = rpack_smooth_slots<T, 3>(true);
+  k.smooth_rpack[3] = rpack_smooth_slots<T, 4>(true);
   k.mass = &launch_mass<T>;
   k.smooth[0] = &launch_smooth<T, 0>;
   k.smooth[1] = &launch_smooth<T, 1>;
