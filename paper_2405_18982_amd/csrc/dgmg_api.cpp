@@ -1332,7 +1332,7 @@ namespace {
 // Times every workgroup shape x XCD numbering of apply and smooth on the
 // finest level with HIP events (best of three batches) and keeps the fastest.
 // Results are cached in a JSON object, one entry per line:
-//   "gfx950/d3/k3/L4/nrhs16/fp64/smooth/l4/v0": {"shape": 0, "remap": 1, "us": 16.50, "rev": 1},
+//   "gfx950/d3/k3/L4/nrhs16/fp64/smooth/l4/v0": {"shape": 0, "remap": 1, "us": 16.50, "rev": 2},
 // v0: the smoother variant the entry was timed with (none for the apply, which all
 // share); rev: kTuneRev of the library that timed it, outside which it is timed
 // again.  Entries without both (written by hand, or before there were any) hold for
@@ -1347,7 +1347,7 @@ std::string tune_key(const dgmg_ctx* c, int nrhs, int prec, const char* kernel) 
 
 // Raised whenever a shape comes to mean another kernel, so that timings of the
 // former one are not kept.
-constexpr int kTuneRev = 1;
+constexpr int kTuneRev = 2;
 
 struct CacheEntry {
   std::string key;
@@ -1408,7 +1408,7 @@ dgmg_status tune_kernel(dgmg_ctx* c, int nrhs, bool smooth, int level, T* x, T* 
   const KernelSet<T>& ks = kset<T>(c);
   const bool rpack = nrhs > 1 && (smooth ? ks.smooth_rpack[c->variant] > 1 : ks.apply_rpack != 0);
   if (smooth) {
-    const bool hi = c->variant == DGMG_SMOOTH_CLAMPED ? ks.smooth_split : ks.smooth_hi_full;
+    const bool hi = c->variant == DGMG_SMOOTH_FULL ? ks.smooth_hi_full : ks.smooth_split;
     const bool direct = ks.smooth_direct && (c->variant == DGMG_SMOOTH_EXACT || c->variant == DGMG_SMOOTH_LOCAL);
     for (int v = 0; v < 12; ++v)
       if ((v < 8 ? v < 4 || hi : rpack) && !(direct && (v & 2))) shapes.push_back(v);

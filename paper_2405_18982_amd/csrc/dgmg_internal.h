@@ -133,8 +133,8 @@ struct KernelSet {
   // the Full kernel
   int smooth_split;
   int smooth_hi_full;
-  // 1 where the Dirichlet smoothers take the direct form, which has neither
-  // prefetch shapes nor two-wave shapes
+  // 1 where the Dirichlet smoothers take the direct form, which has no prefetch
+  // shapes
   int smooth_direct;
   hipError_t (*restrict_residual)(const void* tab, PatchGrid g, T scale, const T* x, const T* b,
                                   T* bc, int nrhs, long long ndof, long long ndof_c,

@@ -1908,8 +1908,36 @@ __device__ __forceinline__ FacePair<T> face_sum(int ty, T l, T r) {
   return FacePair<T>{((ty & 1) ? T(0) : l) + ((ty & 2) ? T(0) : r), l - r};
 }
 
+// Outputs of a line that half H of a two-wave patch forms (H < 0: one wave, all):
+// the even or the odd eigenvectors of an interior line forward, mirrored pairs of
+// nodes back, as the even-odd forms share their sums; the same for every type.
+template <int H>
+__device__ __forceinline__ constexpr bool own_coef(int q) {
+  return H < 0 || (q < kEOH) == (H == 0);
+}
+template <int H>
+__device__ __forceinline__ constexpr bool own_pair(int k) {  // nodes 1 + k and E - 2 - k
+  return H < 0 || (k < (kEOH + 1) / 2) == (H == 0);
+}
+template <int H>
+__device__ __forceinline__ constexpr bool own_node(int p) {
+  return H < 0 || (p == 0 || p == E - 1 ? H == 1 : own_pair<H>(p <= kEOH ? p - 1 : E - 2 - p));
+}
+template <int H, typename T>
+__device__ __forceinline__ void store_coefs(T* s, int base, int stride, const Line<T>& L) {
+#pragma unroll
+  for (int q = 0; q < E; ++q)
+    if (own_coef<H>(q)) s[base + q * stride] = L.v[q];
+}
+template <int H, typename T>
+__device__ __forceinline__ void store_nodes(T* s, int base, int stride, const Line<T>& L) {
+#pragma unroll
+  for (int p = 0; p < E; ++p)
+    if (own_node<H>(p)) s[base + p * stride] = L.v[p];
+}
+
 // o = S^T v - gp F - gt U, the ends and traces of the line as face pairs
-template <typename T, int TY, bool OPQ>
+template <typename T, int TY, bool OPQ, int H>
 __device__ __forceinline__ void line_fwd_t(const Tab<K, T>* __restrict__ t, const Line<T>& v, const FacePair<T>& F,
                                            const FacePair<T>& U, Line<T>& o) {
   using B = FDB<SP_DIR, TY>;
@@ -1919,6 +1947,7 @@ __device__ __forceinline__ void line_fwd_t(const Tab<K, T>* __restrict__ t, cons
   if constexpr (kEO && TY == 0) eo_split<T>(v, vp, vm);
 #pragma unroll
   for (int q = 0; q < E; ++q) {
+    if (!own_coef<H>(q)) continue;
     if (q >= B::QN) {
       o.v[q] = T(0);
       continue;
@@ -1937,7 +1966,7 @@ __device__ __forceinline__ void line_fwd_t(const Tab<K, T>* __restrict__ t, cons
   }
 }
 // o = S (v - gm W), W the dropped end nodes of the line
-template <typename T, int TY, bool OPQ>
+template <typename T, int TY, bool OPQ, int H>
 __device__ __forceinline__ void line_back_t(const Tab<K, T>* __restrict__ t, Line<T>& v, const FacePair<T>& W,
                                             Line<T>& o) {
   using B = FDB<SP_DIR, TY>;
@@ -1952,22 +1981,26 @@ __device__ __forceinline__ void line_back_t(const Tab<K, T>* __restrict__ t, Lin
     T e[kEOH], d[kEOH];
 #pragma unroll
     for (int k = 0; k < kEOH; ++k) {
+      if (!own_pair<H>(k)) continue;
       e[k] = d[k] = T(0);
 #pragma unroll
       for (int q = 0; q < kEOH; ++q) e[k] += S[(1 + k) * E + q] * v.v[q];
 #pragma unroll
       for (int q = 0; q < kEOH; ++q) d[k] += S[(1 + k) * E + kEOH + q] * v.v[kEOH + q];
     }
-    o.v[0] = T(0);
+    if (own_node<H>(0)) o.v[0] = T(0);
 #pragma unroll
-    for (int k = 0; k < kEOH; ++k) o.v[1 + k] = e[k] + d[k];
+    for (int k = 0; k < kEOH; ++k)
+      if (own_pair<H>(k)) o.v[1 + k] = e[k] + d[k];
 #pragma unroll
-    for (int k = kEOH - 1; k >= 0; --k) o.v[E - 2 - k] = e[k] - d[k];
-    o.v[E - 1] = T(0);
+    for (int k = kEOH - 1; k >= 0; --k)
+      if (own_pair<H>(k)) o.v[E - 2 - k] = e[k] - d[k];
+    if (own_node<H>(E - 1)) o.v[E - 1] = T(0);
     return;
   }
 #pragma unroll
   for (int p = 0; p < E; ++p) {
+    if (!own_node<H>(p)) continue;
     T s = T(0);
     if (p >= B::PLO && p < B::PHI) {
 #pragma unroll
@@ -1976,30 +2009,21 @@ __device__ __forceinline__ void line_back_t(const Tab<K, T>* __restrict__ t, Lin
     o.v[p] = s;
   }
 }
-// the x-pass: forward, 1 / (sum lambda), the x-faces' part of w, back
-template <typename T, int TY, bool OPQ>
+// the x-pass: forward, 1 / (sum lambda), the x-faces' part of w, back; sums: the
+// inverse eigenvalue sums of the line, read into r where they were not before
+template <typename T, int TY, bool OPQ, typename Sums>
 __device__ __forceinline__ void line_turn_t(const Tab<K, T>* __restrict__ t, const Line<T>& v, const FacePair<T>& F,
                                             const FacePair<T>& U, const FacePair<T>& W, T inv_scale,
-                                            const T* rs, Line<T>& o) {
-  constexpr int QN = FDB<SP_DIR, TY>::QN;
+                                            const T (&r)[E], Sums sums, Line<T>& o) {
   Line<T> w;
-  T r[QN];
-  if constexpr (!kGsTight<T>) {
+  line_fwd_t<T, TY, OPQ, -1>(t, v, F, U, w);
+  sums();
 #pragma unroll
-    for (int q = 0; q < QN; ++q) r[q] = rs[q * NL];
-  }
-  line_fwd_t<T, TY, OPQ>(t, v, F, U, w);
-  if constexpr (kGsTight<T>) {
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int q = 0; q < QN; ++q) r[q] = rs[q * NL];
-  }
-#pragma unroll
-  for (int q = 0; q < QN; ++q) w.v[q] = w.v[q] * (inv_scale * r[q]);
-  line_back_t<T, TY, OPQ>(t, w, W, o);
+  for (int q = 0; q < FDB<SP_DIR, TY>::QN; ++q) w.v[q] = w.v[q] * (inv_scale * r[q]);
+  line_back_t<T, TY, OPQ, -1>(t, w, W, o);
 }
 // o = S^T M v over the whole line
-template <typename T, int TY>
+template <typename T, int TY, int H>
 __device__ __forceinline__ void line_MS_t(const Tab<K, T>* __restrict__ t, const Line<T>& v, Line<T>& o) {
   const Coef<T> S = pass_coef<T, true>(t->MS[TY]);
   T vp[n], vm[n];
@@ -2012,6 +2036,7 @@ __device__ __forceinline__ void line_MS_t(const Tab<K, T>* __restrict__ t, const
   }
 #pragma unroll
   for (int q = 0; q < E; ++q) {
+    if (!own_coef<H>(q)) continue;
     T s = T(0);
     if (q < FDB<SP_DIR, TY>::QN) {
       if constexpr (TY == 0) {
@@ -2029,45 +2054,46 @@ __device__ __forceinline__ void line_MS_t(const Tab<K, T>* __restrict__ t, const
 // The passes for a patch type known at compile time (INT: an interior patch,
 // type 0 in every direction) or not.  Type 3, both ends on the boundary, does
 // not occur: the smoothers run on meshes of at least four cells a direction.
-template <typename T, bool INT>
+template <typename T, bool INT, int H>
 struct GsLine {
   // an interior patch's passes share S and the couplings where these fit in
   // the scalar registers
   static constexpr bool OPQ = !INT || (2 * kEOH * ((kEO ? kEOH : 2 * kEOH) + 3)) * (int)sizeof(T) > 4 * 72;
   static __device__ __forceinline__ void fwd(const Tab<K, T>* __restrict__ t, int ty, const Line<T>& v,
                                              const FacePair<T>& F, const FacePair<T>& U, Line<T>& o) {
-    if constexpr (INT) return line_fwd_t<T, 0, OPQ>(t, v, F, U, o);
+    if constexpr (INT) return line_fwd_t<T, 0, OPQ, H>(t, v, F, U, o);
     switch (ty) {
-      case 0: line_fwd_t<T, 0, OPQ>(t, v, F, U, o); break;
-      case 1: line_fwd_t<T, 1, OPQ>(t, v, F, U, o); break;
-      default: line_fwd_t<T, 2, OPQ>(t, v, F, U, o); break;
+      case 0: line_fwd_t<T, 0, OPQ, H>(t, v, F, U, o); break;
+      case 1: line_fwd_t<T, 1, OPQ, H>(t, v, F, U, o); break;
+      default: line_fwd_t<T, 2, OPQ, H>(t, v, F, U, o); break;
     }
   }
   static __device__ __forceinline__ void back(const Tab<K, T>* __restrict__ t, int ty, Line<T>& v,
                                               const FacePair<T>& W, Line<T>& o) {
-    if constexpr (INT) return line_back_t<T, 0, OPQ>(t, v, W, o);
+    if constexpr (INT) return line_back_t<T, 0, OPQ, H>(t, v, W, o);
     switch (ty) {
-      case 0: line_back_t<T, 0, OPQ>(t, v, W, o); break;
-      case 1: line_back_t<T, 1, OPQ>(t, v, W, o); break;
-      default: line_back_t<T, 2, OPQ>(t, v, W, o); break;
+      case 0: line_back_t<T, 0, OPQ, H>(t, v, W, o); break;
+      case 1: line_back_t<T, 1, OPQ, H>(t, v, W, o); break;
+      default: line_back_t<T, 2, OPQ, H>(t, v, W, o); break;
     }
   }
+  template <typename Sums>
   static __device__ __forceinline__ void turn(const Tab<K, T>* __restrict__ t, int ty, const Line<T>& v,
                                               const FacePair<T>& F, const FacePair<T>& U, const FacePair<T>& W,
-                                              T inv_scale, const T* rs, Line<T>& o) {
-    if constexpr (INT) return line_turn_t<T, 0, OPQ>(t, v, F, U, W, inv_scale, rs, o);
+                                              T inv_scale, const T (&r)[E], Sums sums, Line<T>& o) {
+    if constexpr (INT) return line_turn_t<T, 0, OPQ>(t, v, F, U, W, inv_scale, r, sums, o);
     switch (ty) {
-      case 0: line_turn_t<T, 0, OPQ>(t, v, F, U, W, inv_scale, rs, o); break;
-      case 1: line_turn_t<T, 1, OPQ>(t, v, F, U, W, inv_scale, rs, o); break;
-      default: line_turn_t<T, 2, OPQ>(t, v, F, U, W, inv_scale, rs, o); break;
+      case 0: line_turn_t<T, 0, OPQ>(t, v, F, U, W, inv_scale, r, sums, o); break;
+      case 1: line_turn_t<T, 1, OPQ>(t, v, F, U, W, inv_scale, r, sums, o); break;
+      default: line_turn_t<T, 2, OPQ>(t, v, F, U, W, inv_scale, r, sums, o); break;
     }
   }
   static __device__ __forceinline__ void ms(const Tab<K, T>* __restrict__ t, int ty, const Line<T>& v, Line<T>& o) {
-    if constexpr (INT) return line_MS_t<T, 0>(t, v, o);
+    if constexpr (INT) return line_MS_t<T, 0, H>(t, v, o);
     switch (ty) {
-      case 0: line_MS_t<T, 0>(t, v, o); break;
-      case 1: line_MS_t<T, 1>(t, v, o); break;
-      default: line_MS_t<T, 2>(t, v, o); break;
+      case 0: line_MS_t<T, 0, H>(t, v, o); break;
+      case 1: line_MS_t<T, 1, H>(t, v, o); break;
+      default: line_MS_t<T, 2, H>(t, v, o); break;
     }
   }
 };
@@ -2114,15 +2140,17 @@ __device__ __forceinline__ T& at32(T* p, unsigned o) {
 // patch's own end value.  ZERO: x = 0 on entry, so there are no faces, and
 // every node of the tile is written.  INT: the patch is an interior one.
 // GUARD: the launch has patches that look at their old values, this one if guard.
+// H: half of a two-wave patch (k_smooth_split), -1: the patch is one wave's work.
 //
 // Order of the loads: the face layers and lines, then (where the registers
 // allow it) b, all before the first of them is used -- one memory round trip.
-template <typename T, int MODE, bool ZERO, bool INT, bool GUARD>
+template <typename T, int MODE, bool ZERO, bool INT, bool GUARD, int H = -1>
 __device__ __forceinline__ void gs_body(const Tab<K, T>* __restrict__ t, int N, const PatchPos& P, T scale,
                                         T inv_scale, T* __restrict__ xr, const T* __restrict__ br, bool active,
                                         int lane, T* A, bool guard) {
   static_assert(NL == TPP && NF == TPP, "one line and one face node per lane");
-  using L1 = GsLine<T, INT>;
+  static_assert(H < 0 || (D == 3 && TPP % 64 == 0), "halves of whole waves");
+  using L1 = GsLine<T, INT, H>;
   const int tyx = INT ? 0 : P.ty[0], tyy = INT ? 0 : P.ty[1], tyl = INT ? 0 : P.ty[D - 1];
   // The lane's coordinates (a, q): in 3-D the lanes run through the plane cell
   // by cell (cell and node an, am of a; qn, qm of q), as the vectors do, so that
@@ -2196,9 +2224,9 @@ __device__ __forceinline__ void gs_body(const Tab<K, T>* __restrict__ t, int N, 
     }
     if (active) {
       raw[0] = at32(x0, lo);
-      raw[1] = ownl ? raw[0] : at32(x0 - lc, lo + K * ln);
+      if (H <= 0) raw[1] = ownl ? raw[0] : at32(x0 - lc, lo + K * ln);
       raw[2] = at32(x1, lo + K * ln);
-      raw[3] = ownr ? raw[2] : at32(x1 + lc, lo);
+      if (H != 0) raw[3] = ownr ? raw[2] : at32(x1 + lc, lo);
     }
     if constexpr (D == 3) {
       // lines along z of the y-faces (field f = 0..3: left end, left trace,
@@ -2206,7 +2234,7 @@ __device__ __forceinline__ void gs_body(const Tab<K, T>* __restrict__ t, int N, 
       // S_z^T M_z into planes f; the raw z-layers into planes 8..11
       if (active) {
         const T* xm = x0 - cy - NC;
-        if (ROWLDS && lane < n * n) A[kGsM + lane] = kMassRows<T>.v[lane];
+        if (ROWLDS && H <= 0 && lane < n * n) A[kGsM + lane] = kMassRows<T>.v[lane];
 #pragma unroll
         for (int li0 = 0; li0 < 8 * E; li0 += TPP) {
           const int li = li0 + lane;
@@ -2230,11 +2258,11 @@ __device__ __forceinline__ void gs_body(const Tab<K, T>* __restrict__ t, int N, 
           if (!TIGHT && li0 == 0) load_b();
           if (WARM && li0 == 0) warm_wait(warm);
           L1::ms(t, tyl, v, w);
-#pragma unroll
-          for (int p = 0; p < E; ++p) A[f * SZ + p * SY + i] = w.v[p];
+          store_coefs<H>(A, f * SZ + i, SY, w);
         }
 #pragma unroll
-        for (int f = 0; f < 4; ++f) A[(8 + f) * SZ + q * SY + a] = raw[f];
+        for (int f = 0; f < 4; ++f)
+          if (H < 0 || f / 2 == H) A[(8 + f) * SZ + q * SY + a] = raw[f];
         if (GUARD && guard) {
 #pragma unroll
           for (int p = 0; p < E; ++p) nonf += T(0) * old.v[p];
@@ -2257,7 +2285,7 @@ __device__ __forceinline__ void gs_body(const Tab<K, T>* __restrict__ t, int N, 
           for (int nu = 0; nu < n; ++nu) s += rowx[nu] * rx[(8 + f) * SZ + nu];
 #pragma unroll
           for (int nu = 0; nu < n; ++nu) u += rowx[nu] * rx[f * SZ + nu];
-          A[(12 + f) * SZ + q * SY + a] = s;
+          if (H <= 0) A[(12 + f) * SZ + q * SY + a] = s;
           ym[f] = scale * u;
           if constexpr (TIGHT) __builtin_amdgcn_sched_barrier(0);
         }
@@ -2269,12 +2297,12 @@ __device__ __forceinline__ void gs_body(const Tab<K, T>* __restrict__ t, int N, 
 #pragma unroll
         for (int li0 = 0; li0 < 4 * E; li0 += TPP) {
           const int li = li0 + lane - first;
-          if (li < 0 || li >= 4 * E) continue;
+          if (H == 0 || li < 0 || li >= 4 * E) continue;
           const int f = small_div<E>(li);
           T* r = A + (4 + f) * SZ + (li - f * E) * SY;
           Line<T> v, w;
           load_line(r, 0, 1, v);
-          L1::ms(t, tyy, v, w);
+          GsLine<T, INT, -1>::ms(t, tyy, v, w);  // whole lines, in place
           store_line(r, 0, 1, w);
         }
         if constexpr (TIGHT) load_b();
@@ -2357,38 +2385,74 @@ __device__ __forceinline__ void gs_body(const Tab<K, T>* __restrict__ t, int N, 
   // where this lane's lines along x, y and the last direction start in the tile
   const int bx = a * SY + q * SZ, by = a + q * SZ, bz = (D == 3) ? a + q * SY : a;
   constexpr int sl = (D == 3) ? SZ : SY;
+  // two waves read whole lines and each writes its outputs: two tiles in turn
+  T* Z = A;
+  T* B = H < 0 ? Z : A + TS;
+  // inverse eigenvalue sums of the lane's x-line (qy, qz) = (a, q): asked for two
+  // passes ahead (3-D Q2 FP64, 8^3 cells: a step 45.2 -> 43.7 us), or where registers
+  // are short only when needed
+  constexpr bool LATE = TIGHT && H < 0;
+  T r[E];
+  auto load_sums = [&]() {
+    const T* rs = &at32(t->rs[0][(D == 3) ? (tyx * 4 + tyy) * 4 + tyl : tyx * 4 + tyy], (unsigned)lane);
+#pragma unroll
+    for (int c = 0; c < E; ++c)
+      if (own_coef<H>(c)) r[c] = rs[c * NL];
+  };
+  auto late_sums = [&]() {
+    if constexpr (LATE) {
+      __builtin_amdgcn_sched_barrier(0);
+      load_sums();
+    }
+  };
   // last direction: S^T b - its faces
   if (active) {
     Line<T> o;
+    if constexpr (!LATE) load_sums();
     if constexpr (GUARD) bl.v[n] += nonf;  // node n is in every V
     L1::fwd(t, tyl, bl, Fl, Ul, o);
-    store_line(A, bz, sl, o);
+    store_coefs<H>(Z, bz, sl, o);
   }
   __syncthreads();
   if constexpr (D == 3) {
     if (active) {
       Line<T> v, o;
-      load_line(A, by, SY, v);
+      load_line(Z, by, SY, v);
       L1::fwd(t, tyy, v, Fy, Uy, o);
-      store_line(A, by, SY, o);
+      store_coefs<H>(B, by, SY, o);
     }
     __syncthreads();
   }
   if (active) {
-    // x-line (qy, qz) = (a, q) and its inverse eigenvalue sums
-    const T* rs = &at32(t->rs[0][(D == 3) ? (tyx * 4 + tyy) * 4 + tyl : tyx * 4 + tyy], (unsigned)lane);
+    const FacePair<T> Fx{scale * Wx.s, scale * Wx.d};
     Line<T> v, o;
-    load_line(A, bx, 1, v);
-    L1::turn(t, tyx, v, FacePair<T>{scale * Wx.s, scale * Wx.d}, Ux, Wx, inv_scale, rs, o);
-    store_line(A, bx, 1, o);
+    load_line(B, bx, 1, v);
+    if constexpr (H < 0) {
+      L1::turn(t, tyx, v, Fx, Ux, Wx, inv_scale, r, late_sums, o);
+    } else {
+      L1::fwd(t, tyx, v, Fx, Ux, o);
+#pragma unroll
+      for (int c = 0; c < E; ++c)
+        if (own_coef<H>(c)) o.v[c] = o.v[c] * (inv_scale * r[c]);
+    }
+    store_coefs<H>(Z, bx, 1, o);
   }
   __syncthreads();
+  if constexpr (H >= 0) {
+    if (active) {
+      Line<T> v, o;
+      load_line(Z, bx, 1, v);
+      L1::back(t, tyx, v, Wx, o);
+      store_nodes<H>(B, bx, 1, o);
+    }
+    __syncthreads();
+  }
   if constexpr (D == 3) {
     if (active) {
       Line<T> v, o;
-      load_line(A, by, SY, v);
+      load_line(B, by, SY, v);
       L1::back(t, tyy, v, Wy, o);
-      store_line(A, by, SY, o);
+      store_nodes<H>(Z, by, SY, o);
     }
     __syncthreads();
   }
@@ -2398,11 +2462,11 @@ __device__ __forceinline__ void gs_body(const Tab<K, T>* __restrict__ t, int N, 
                                   (D == 2 || ((q > 0 || (tyy & 1)) && (q < E - 1 || (tyy & 2)))));
   if (active && keep_line) {
     Line<T> v, o;
-    load_line(A, bz, sl, v);
+    load_line(Z, bz, sl, v);
     L1::back(t, tyl, v, Wl, o);
 #pragma unroll
     for (int p = 0; p < E; ++p) {
-      if (!ZERO && ((p == 0 && !(tyl & 1)) || (p == E - 1 && !(tyl & 2)))) continue;
+      if (!own_node<H>(p) || (!ZERO && ((p == 0 && !(tyl & 1)) || (p == E - 1 && !(tyl & 2))))) continue;
       at32(p < n ? x0 : x1, lo + (p % n) * ln) = o.v[p];
     }
   }
@@ -2615,17 +2679,18 @@ __device__ __forceinline__ void smooth_body(const Tab<K, T>* __restrict__ t, con
 
 // Waves per SIMD the register allocation of k_smooth aims at (1: no aim): for
 // the direct form in 3-D the most an interior patch's passes allow without
-// spills.
-template <typename T, int MODE, int THREADS>
+// spilled vector registers (scalar ones spill to vector lanes: 99 for Q3 FP64, 121 for
+// Q7 FP32).
+template <typename T, int MODE, int THREADS, bool GUARD>
 constexpr int smooth_waves() {
   if (D != 3 || !kDirect<MODE> || THREADS > 256) return 1;
   if (sizeof(T) == 8) return K <= 4 ? 4 : 2;
-  return K <= 3 ? 8 : K == 4 ? 6 : K == 6 ? 4 : 5;
+  return K <= 3 ? (GUARD ? 7 : 8) : K == 4 ? 6 : K == 6 ? 4 : 5;
 }
 // LDS a workgroup of several right-hand sides may take: half a CU's
 constexpr int kPackedLDS = 80 * 1024;
 template <typename T, int PPB, int MODE, bool PREFETCH, bool ZERO = false, bool RP = false, bool GUARD = false>
-__global__ void __launch_bounds__(TPP * PPB, (smooth_waves<T, MODE, TPP * PPB>()))
+__global__ void __launch_bounds__(TPP * PPB, (smooth_waves<T, MODE, TPP * PPB, GUARD>()))
 k_smooth(const Tab<K, T>* __restrict__ t, PatchGrid g, T scale, T inv_scale,
          const T* __restrict__ xin, T* __restrict__ xout, const T* __restrict__ b, long long ndof) {
   constexpr int PP = smooth_pp<MODE, T>();
@@ -3040,22 +3105,55 @@ __device__ __forceinline__ void smooth_split_body(const Tab<K, T>* __restrict__ 
   }
 }
 
-template <typename T, int PPB, int MODE, bool PREFETCH, bool ZERO = false>
+// Half H of a patch in any of the two-wave smoothers.  The direct form divides its
+// lines' outputs over the halves by own_coef and own_node: what a wave does in a
+// pass is halved, the x-pass becomes two, and a patch takes two tiles.  Bound by
+// the latency of one patch's phases on levels of few patches, which is where the
+// tuner takes it, V-cycles with two waves / one on every level: 3-D Q3 FP32 8^3 95.5 /
+// 99.8 us, 16^3 183 / 190, FP64 116 / 120 and 219 / 223 us, Q7 FP32 8^3 365 / 401, 16^3 606 /
+// 642 us; with many patches one wave is faster (Q3 FP64 32^3 475 / 434 us).  Both forms
+// of an output have the operations of one wave in the same order, so the results
+// are bitwise those of k_smooth.
+template <typename T, int MODE, bool PREFETCH, bool ZERO, bool GUARD, int H>
+__device__ __forceinline__ void smooth_half(const Tab<K, T>* __restrict__ t, const PatchGrid& g, T scale,
+                                            T inv_scale, T* __restrict__ x, const T* __restrict__ b,
+                                            long long ndof, int pid, int lane, T* sm, int rhs) {
+  if constexpr (MODE == 4) {
+    smooth_split_body<T, MODE, PREFETCH, ZERO, H>(t, g, scale, inv_scale, x, b, ndof, pid, lane, sm, rhs);
+  } else {
+    static_assert(kDirect<MODE>, "clamped kernel or direct form");
+    const bool act = pid < g.npatch;
+    const PatchPos P = patch_pos(g, act ? pid : 0);
+    T* xv = x + (long long)rhs * ndof;
+    const T* bv = b + (long long)rhs * ndof;
+    if ((P.ty[0] | P.ty[1] | P.ty[2]) == 0)
+      gs_body<T, MODE, ZERO, true, GUARD, H>(t, g.N, P, scale, inv_scale, xv, bv, act, lane, sm, g.guard == 2);
+    else
+      gs_body<T, MODE, ZERO, false, GUARD, H>(t, g.N, P, scale, inv_scale, xv, bv, act, lane, sm, true);
+  }
+}
+// LDS per two-wave patch: two tiles
+template <int MODE, typename T = double>
+constexpr int split_pp() {
+  return smooth_pp<MODE, T>() > 2 * TS ? smooth_pp<MODE, T>() : 2 * TS;
+}
+
+template <typename T, int PPB, int MODE, bool PREFETCH, bool ZERO = false, bool GUARD = false>
 __global__ void __launch_bounds__(2 * TPP * PPB)
 k_smooth_split(const Tab<K, T>* __restrict__ t, PatchGrid g, T scale, T inv_scale, T* __restrict__ x,
                const T* __restrict__ b, long long ndof) {
-  constexpr int PP = smooth_pp<MODE, T>();
+  constexpr int PP = split_pp<MODE, T>();
   __shared__ T smem[PPB * PP];
   const int w = (int)threadIdx.x / TPP;  // wave group: slot * 2 + half
   const int ws = kSplitOK ? __builtin_amdgcn_readfirstlane(w) : w;
   const int slot = ws / 2, h = ws % 2, lane = threadIdx.x % TPP;
   const int pid = xcd_block(blockIdx.x, gridDim.x, g.xcd_remap) * PPB + slot;
   if (h == 0)
-    smooth_split_body<T, MODE, PREFETCH, ZERO, 0>(t, g, scale, inv_scale, x, b, ndof, pid, lane,
-                                                  smem + slot * PP, blockIdx.y);
+    smooth_half<T, MODE, PREFETCH, ZERO, GUARD, 0>(t, g, scale, inv_scale, x, b, ndof, pid, lane,
+                                                   smem + slot * PP, blockIdx.y);
   else
-    smooth_split_body<T, MODE, PREFETCH, ZERO, 1>(t, g, scale, inv_scale, x, b, ndof, pid, lane,
-                                                  smem + slot * PP, blockIdx.y);
+    smooth_half<T, MODE, PREFETCH, ZERO, GUARD, 1>(t, g, scale, inv_scale, x, b, ndof, pid, lane,
+                                                   smem + slot * PP, blockIdx.y);
 }
 
 // ------------------------------------------------- residual + restriction
@@ -3613,11 +3711,11 @@ hipError_t launch_mass(const void* tab, PatchGrid g, T scale, const T* x, T* y, 
   return hipGetLastError();
 }
 // smoother shapes: bit 0 selects the workgroup shape, bit 1 the prefetch of b
-// (not in the direct form, which has one order of loads), bit 2
-// two waves per patch where kSplitOK (clamped kernel), else one patch per
-// workgroup where several patches share a wave (2-D, 3-D Q1: patches of different types there
-// run their fast-diagonalisation branches one after the other), else the same
-// as bit 2 clear; variant 0 / 1 / 2 / 3: Dirichlet consistent / Dirichlet with
+// (not in the direct form, which has one order of loads), bit 2 two waves per
+// patch where kSplitOK (not the Full kernel), else one patch per workgroup where
+// several patches share a wave (2-D, 3-D Q1: patches of different types there run
+// their fast-diagonalisation branches one after the other), else the same as
+// bit 2 clear; variant 0 / 1 / 2 / 3: Dirichlet consistent / Dirichlet with
 // the paper's residual / Full / clamped
 constexpr bool kOnePatchShape = !kSplitOK && PPB_DEFAULT > 1;
 // shapes 8..11 (bit 3): one patch for several right-hand sides per workgroup,
@@ -3645,6 +3743,21 @@ hipError_t launch_smooth_rpack(const Tab<K, T>* tb, PatchGrid g, T scale, T inv_
                        xout, b, ndof);
   return hipGetLastError();
 }
+template <typename T, int PPB, int MODE, bool PF>
+hipError_t launch_smooth_split(const Tab<K, T>* tb, PatchGrid g, T scale, T inv_scale, int zero, T* x, const T* b,
+                               int nrhs, long long ndof, hipStream_t s) {
+  constexpr bool PFD = PF && !kDirect<MODE>;
+  const dim3 grid((g.npatch + PPB - 1) / PPB, nrhs), block(2 * TPP * PPB);
+  if (zero)
+    hipLaunchKernelGGL((k_smooth_split<T, PPB, MODE, false, true>), grid, block, 0, s, tb, g, scale, inv_scale, x, b,
+                       ndof);
+  else if (kDirect<MODE> && g.guard)
+    hipLaunchKernelGGL((k_smooth_split<T, PPB, MODE, PFD, false, kDirect<MODE>>), grid, block, 0, s, tb, g, scale,
+                       inv_scale, x, b, ndof);
+  else
+    hipLaunchKernelGGL((k_smooth_split<T, PPB, MODE, PFD>), grid, block, 0, s, tb, g, scale, inv_scale, x, b, ndof);
+  return hipGetLastError();
+}
 template <typename T, int V>
 hipError_t launch_smooth(const void* tab, PatchGrid g, T scale, T inv_scale, int variant, int zero,
                          const T* xin, T* xout, const T* b, int nrhs, long long ndof, hipStream_t s) {
@@ -3665,16 +3778,9 @@ hipError_t launch_smooth(const void* tab, PatchGrid g, T scale, T inv_scale, int
   }
   dim3 grid((g.npatch + PPB - 1) / PPB, nrhs);
   if constexpr (SPLIT) {
-    if (variant == 3) {
-      const dim3 block(2 * TPP * PPB);
-      if (zero)
-        hipLaunchKernelGGL((k_smooth_split<T, PPB, 4, false, true>), grid, block, 0, s, tb, g, scale,
-                           inv_scale, xout, b, ndof);
-      else
-        hipLaunchKernelGGL((k_smooth_split<T, PPB, 4, PF>), grid, block, 0, s, tb, g, scale, inv_scale,
-                           xout, b, ndof);
-      return hipGetLastError();
-    }
+    if (variant == 0) return launch_smooth_split<T, PPB, 1, PF>(tb, g, scale, inv_scale, zero, xout, b, nrhs, ndof, s);
+    if (variant == 1) return launch_smooth_split<T, PPB, 2, PF>(tb, g, scale, inv_scale, zero, xout, b, nrhs, ndof, s);
+    if (variant == 3) return launch_smooth_split<T, PPB, 4, PF>(tb, g, scale, inv_scale, zero, xout, b, nrhs, ndof, s);
   }
   if (zero) {  // x = 0, colour 0: the residual is b, no prefetch needed
     if (variant == 2)
