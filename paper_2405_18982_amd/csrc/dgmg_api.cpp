@@ -101,13 +101,11 @@ void fill_tab(int dim, const dgmg::HostTables& H, std::vector<unsigned char>& ou
       for (int ty = 0; ty < 4; ++ty) {
         const std::vector<double>& lx = lams[sp][tx];
         const std::vector<double>& ly = lams[sp][ty];
-        if (sp == 0 && dim == 2 && dgmg::direct_smoother(2, K)) {
-          for (int qx = 0; qx < E; ++qx)
-            for (int qy = 0; qy < E; ++qy) t->rs[0][tx * 4 + ty][qx * E + qy] = (T)inv(lx[qx] + ly[qy]);
-          continue;
-        }
         if (dim == 2) {
-          T* r = t->rs[sp][tx * 4 + ty];
+          if (sp == 0)
+            for (int qx = 0; qx < E; ++qx)
+              for (int qy = 0; qy < E; ++qy) t->rs[0][tx * 4 + ty][qx * E + qy] = (T)inv(lx[qx] + ly[qy]);
+          T* r = t->rs[sp][tx * 4 + ty + (sp == 0 ? 16 : 0)];
           for (int qy = 0; qy < E; ++qy)
             for (int qx = 0; qx < E; ++qx) r[qy * E + qx] = (T)inv(lx[qx] + ly[qy]);
           continue;
@@ -1409,7 +1407,7 @@ dgmg_status tune_kernel(dgmg_ctx* c, int nrhs, bool smooth, int level, T* x, T* 
   const bool rpack = nrhs > 1 && (smooth ? ks.smooth_rpack[c->variant] > 1 : ks.apply_rpack != 0);
   if (smooth) {
     const bool hi = c->variant == DGMG_SMOOTH_FULL ? ks.smooth_hi_full : ks.smooth_split;
-    const bool direct = ks.smooth_direct && (c->variant == DGMG_SMOOTH_EXACT || c->variant == DGMG_SMOOTH_LOCAL);
+    const bool direct = c->lv[level].N < ks.direct_below && (c->variant == DGMG_SMOOTH_EXACT || c->variant == DGMG_SMOOTH_LOCAL);
     for (int v = 0; v < 12; ++v)
       if ((v < 8 ? v < 4 || hi : rpack) && !(direct && (v & 2))) shapes.push_back(v);
   } else {

@@ -24,6 +24,19 @@ constexpr int kSmoothShapes = 12;
 // and 109.4 us directly; 2-D Q2 on 8^2 cells 16.4 against 17.6 us, 2-D Q3 on 64^2
 // (three right-hand sides) 21.3 both, 2-D Q7 on 128^2 53.0 against 40.3 us.
 constexpr bool direct_smoother(int dim, int k) { return dim == 3 ? k >= 2 : k >= 4; }
+// Only levels with fewer cells a direction than this do.  In 2-D the direct form
+// reads and writes lines along y, a cell row in FP32 20 to 28 bytes for Q4..Q6, where
+// the residual form has x-lines; that costs nothing while a level sits in the
+// caches and few patches wait on their phases, and up to a third where it is bound by
+// memory.  FP32 smoothing steps, direct / residual form: Q4 64^2 cells 21.1 / 21.1 us, 256^2
+// 37.8 / 35.3, 512^2 94.7 / 81.2; Q5 128^2 27.4 / 29.8, 256^2 48.8 / 47.8, 512^2 117.6 / 105.9;
+// Q6 64^2 25.7 / 26.9, 128^2 31.8 / 31.9 (with 16 right-hand sides 171 / 144), 256^2 61.3 /
+// 56.1, 1024^2 822 / 626; Q7, whose rows are whole 32 bytes, 128^2 33.1 / 36.6, 512^2 163 /
+// 164.  FP64 and 3-D: direct everywhere.
+constexpr int kAllLevels = 1 << 30;
+constexpr int direct_below(int dim, int k, int bytes) {
+  return dim == 2 && bytes == 4 && k >= 4 && k <= 6 ? (k == 5 ? 256 : 128) : kAllLevels;
+}
 
 // Reference (h = 1, kappa = 1) data of Q_K on a two-cell patch that depends
 // on the penalty, in the arithmetic type T of the kernels that read them.
@@ -48,7 +61,7 @@ constexpr bool direct_smoother(int dim, int k) { return dim == 3 ? k >= 2 : k >=
 //         rs[0][c][qx E^2 + l] of the x-line (qy, qz) of lane l, the lanes
 //         running through the plane cell by cell (qy = (l' mod 2) n + i mod n,
 //         qz = (l' div 2) n + i div n with l' = l div n^2, i = l mod n^2); in
-//         2-D rs[0][c][qx E + qy].
+//         2-D rs[0][c][qx E + qy], and the other order in rs[0][16 + c].
 template <int K, typename T>
 struct Tab {
   static constexpr int n = K + 1;
@@ -133,9 +146,9 @@ struct KernelSet {
   // the Full kernel
   int smooth_split;
   int smooth_hi_full;
-  // 1 where the Dirichlet smoothers take the direct form, which has no prefetch
-  // shapes
-  int smooth_direct;
+  // levels with fewer cells a direction take the direct form of the Dirichlet
+  // smoothers, which has no prefetch shapes (0: none)
+  int direct_below;
   hipError_t (*restrict_residual)(const void* tab, PatchGrid g, T scale, const T* x, const T* b,
                                   T* bc, int nrhs, long long ndof, long long ndof_c,
                                   hipStream_t s);

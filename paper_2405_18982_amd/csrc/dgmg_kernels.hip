@@ -487,7 +487,7 @@ template <typename T, int SP>
 __device__ __forceinline__ void load_rs(const Tab<K, T>* __restrict__ t, const int (&ty)[3], int l,
                                         T (&r)[E]) {
   const int combo = (D == 3) ? (ty[0] * 4 + ty[1]) * 4 + ty[2] : ty[0] * 4 + ty[1];
-  const T* p = t->rs[SP == SP_FULL ? 1 : SP == SP_CLAMPED ? 2 : 0][combo] + l * E;
+  const T* p = t->rs[SP == SP_FULL ? 1 : SP == SP_CLAMPED ? 2 : 0][combo + (D == 2 && SP == SP_DIR ? 16 : 0)] + l * E;
 #pragma unroll
   for (int q = 0; q < E; ++q) r[q] = p[q];
 }
@@ -1855,6 +1855,10 @@ constexpr bool kFullOnApplyRF = kApplyRF && !kFullRF;
 // direct_smoother says so.
 template <int MODE>
 constexpr bool kDirect = (MODE == 1 || MODE == 2) && direct_smoother(D, K);
+// MODE 5, 6: MODE 1, 2 by operator passes, on the levels where direct_below has the
+// direct form give way
+template <typename T>
+constexpr bool kBothForms = direct_smoother(D, K) && direct_below(D, K, sizeof(T)) != kAllLevels;
 
 // LDS of the direct form per patch: the tile, whose space first holds the face
 // fields -- in 3-D 16 planes of E x E values with the tile's row and plane
@@ -2496,7 +2500,8 @@ __device__ __forceinline__ void smooth_body(const Tab<K, T>* __restrict__ t, con
   } else {
   constexpr bool FULL = (MODE == 3);
   constexpr int SP = FULL ? SP_FULL : (MODE == 4) ? SP_CLAMPED : SP_DIR;
-  constexpr int OPM = FULL ? 0 : (MODE == 4) ? 2 : MODE;  // operator-pass mode (side data)
+  // operator-pass mode (side data)
+  constexpr int OPM = FULL ? 0 : (MODE == 4) ? 2 : MODE > 4 ? MODE - 4 : MODE;
   const bool inrange = pid < g.npatch;
   T* A = sm;
   T* B = A + TS;
@@ -3758,64 +3763,53 @@ hipError_t launch_smooth_split(const Tab<K, T>* tb, PatchGrid g, T scale, T inv_
     hipLaunchKernelGGL((k_smooth_split<T, PPB, MODE, PFD>), grid, block, 0, s, tb, g, scale, inv_scale, x, b, ndof);
   return hipGetLastError();
 }
+template <typename T, int PPB, int MODE, bool PF>
+hipError_t launch_smooth_patches(const Tab<K, T>* tb, PatchGrid g, T scale, T inv_scale, int zero, const T* xin,
+                                 T* xout, const T* b, int nrhs, long long ndof, hipStream_t s) {
+  constexpr bool PFD = PF && !kDirect<MODE>;
+  const dim3 grid((g.npatch + PPB - 1) / PPB, nrhs), block(TPP * PPB);
+  if (zero)  // x = 0, colour 0: the residual is b, no prefetch needed
+    hipLaunchKernelGGL((k_smooth<T, PPB, MODE, false, true>), grid, block, 0, s, tb, g, scale, inv_scale, xin, xout,
+                       b, ndof);
+  else if (kDirect<MODE> && g.guard)
+    hipLaunchKernelGGL((k_smooth<T, PPB, MODE, PFD, false, false, kDirect<MODE>>), grid, block, 0, s, tb, g, scale,
+                       inv_scale, xin, xout, b, ndof);
+  else
+    hipLaunchKernelGGL((k_smooth<T, PPB, MODE, PFD>), grid, block, 0, s, tb, g, scale, inv_scale, xin, xout, b, ndof);
+  return hipGetLastError();
+}
+// shape V of one kernel
+template <typename T, int V, int MODE>
+hipError_t launch_smooth_mode(const Tab<K, T>* tb, PatchGrid g, T scale, T inv_scale, int zero, const T* xin, T* xout,
+                              const T* b, int nrhs, long long ndof, hipStream_t s) {
+  constexpr int PPB = (kOnePatchShape && (V & 4)) ? 1 : Shape<(V & 1)>::PPB;
+  constexpr bool PF = (V & 2) != 0;
+  if constexpr ((V & 8) != 0)
+    return launch_smooth_rpack<T, MODE, (V & 1) != 0, PF>(tb, g, scale, inv_scale, zero, xin, xout, b, nrhs, ndof, s);
+  else if constexpr ((V & 4) != 0 && kSplitOK && MODE != 3)
+    return launch_smooth_split<T, PPB, MODE, PF>(tb, g, scale, inv_scale, zero, xout, b, nrhs, ndof, s);
+  else
+    return launch_smooth_patches<T, PPB, MODE, PF>(tb, g, scale, inv_scale, zero, xin, xout, b, nrhs, ndof, s);
+}
 template <typename T, int V>
 hipError_t launch_smooth(const void* tab, PatchGrid g, T scale, T inv_scale, int variant, int zero,
                          const T* xin, T* xout, const T* b, int nrhs, long long ndof, hipStream_t s) {
-  constexpr int PPB = (kOnePatchShape && (V & 4)) ? 1 : Shape<(V & 1)>::PPB;
-  constexpr bool PF = (V & 2) != 0, PFD = PF && !kDirect<1>;
-  constexpr bool SPLIT = (V & 4) != 0 && kSplitOK;
   g.nrhs = nrhs;
   const Tab<K, T>* tb = (const Tab<K, T>*)tab;
-  if constexpr ((V & 8) != 0) {
-    constexpr bool LG = (V & 1) != 0;
-    if (variant == 2)
-      return launch_smooth_rpack<T, 3, LG, PF>(tb, g, scale, inv_scale, zero, xin, xout, b, nrhs, ndof, s);
-    if (variant == 3)
-      return launch_smooth_rpack<T, 4, LG, PF>(tb, g, scale, inv_scale, zero, xout, xout, b, nrhs, ndof, s);
-    if (variant == 1)
-      return launch_smooth_rpack<T, 2, LG, PF>(tb, g, scale, inv_scale, zero, xout, xout, b, nrhs, ndof, s);
-    return launch_smooth_rpack<T, 1, LG, PF>(tb, g, scale, inv_scale, zero, xout, xout, b, nrhs, ndof, s);
-  }
-  dim3 grid((g.npatch + PPB - 1) / PPB, nrhs);
-  if constexpr (SPLIT) {
-    if (variant == 0) return launch_smooth_split<T, PPB, 1, PF>(tb, g, scale, inv_scale, zero, xout, b, nrhs, ndof, s);
-    if (variant == 1) return launch_smooth_split<T, PPB, 2, PF>(tb, g, scale, inv_scale, zero, xout, b, nrhs, ndof, s);
-    if (variant == 3) return launch_smooth_split<T, PPB, 4, PF>(tb, g, scale, inv_scale, zero, xout, b, nrhs, ndof, s);
-  }
-  if (zero) {  // x = 0, colour 0: the residual is b, no prefetch needed
-    if (variant == 2)
-      hipLaunchKernelGGL((k_smooth<T, PPB, 3, false, true>), grid, dim3(TPP * PPB), 0, s, tb, g,
-                         scale, inv_scale, xin, xout, b, ndof);
-    else if (variant == 3)
-      hipLaunchKernelGGL((k_smooth<T, PPB, 4, false, true>), grid, dim3(TPP * PPB), 0, s, tb, g,
-                         scale, inv_scale, xout, xout, b, ndof);
-    else if (variant == 1)
-      hipLaunchKernelGGL((k_smooth<T, PPB, 2, false, true>), grid, dim3(TPP * PPB), 0, s, tb, g,
-                         scale, inv_scale, xout, xout, b, ndof);
-    else
-      hipLaunchKernelGGL((k_smooth<T, PPB, 1, false, true>), grid, dim3(TPP * PPB), 0, s, tb, g,
-                         scale, inv_scale, xout, xout, b, ndof);
-    return hipGetLastError();
-  }
   if (variant == 2)
-    hipLaunchKernelGGL((k_smooth<T, PPB, 3, PF>), grid, dim3(TPP * PPB), 0, s, tb, g, scale,
-                       inv_scale, xin, xout, b, ndof);
-  else if (variant == 3)
-    hipLaunchKernelGGL((k_smooth<T, PPB, 4, PF>), grid, dim3(TPP * PPB), 0, s, tb, g, scale,
-                       inv_scale, xout, xout, b, ndof);
-  else if (variant == 1 && kDirect<1> && g.guard)
-    hipLaunchKernelGGL((k_smooth<T, PPB, 2, PFD, false, false, kDirect<1>>), grid, dim3(TPP * PPB), 0, s, tb, g,
-                       scale, inv_scale, xout, xout, b, ndof);
-  else if (variant == 1)
-    hipLaunchKernelGGL((k_smooth<T, PPB, 2, PFD>), grid, dim3(TPP * PPB), 0, s, tb, g, scale,
-                       inv_scale, xout, xout, b, ndof);
-  else if (kDirect<1> && g.guard)
-    hipLaunchKernelGGL((k_smooth<T, PPB, 1, PFD, false, false, kDirect<1>>), grid, dim3(TPP * PPB), 0, s, tb, g,
-                       scale, inv_scale, xout, xout, b, ndof);
-  else
-    hipLaunchKernelGGL((k_smooth<T, PPB, 1, PFD>), grid, dim3(TPP * PPB), 0, s, tb, g, scale,
-                       inv_scale, xout, xout, b, ndof);
-  return hipGetLastError();
+    return launch_smooth_mode<T, V, 3>(tb, g, scale, inv_scale, zero, xin, xout, b, nrhs, ndof, s);
+  if (variant == 3)
+    return launch_smooth_mode<T, V, 4>(tb, g, scale, inv_scale, zero, xout, xout, b, nrhs, ndof, s);
+  if constexpr (kBothForms<T>) {
+    if (g.N >= direct_below(D, K, sizeof(T))) {
+      if (variant == 1)
+        return launch_smooth_mode<T, V, 6>(tb, g, scale, inv_scale, zero, xout, xout, b, nrhs, ndof, s);
+      return launch_smooth_mode<T, V, 5>(tb, g, scale, inv_scale, zero, xout, xout, b, nrhs, ndof, s);
+    }
+  }
+  if (variant == 1)
+    return launch_smooth_mode<T, V, 2>(tb, g, scale, inv_scale, zero, xout, xout, b, nrhs, ndof, s);
+  return launch_smooth_mode<T, V, 1>(tb, g, scale, inv_scale, zero, xout, xout, b, nrhs, ndof, s);
 }
 template <typename T>
 hipError_t launch_restrict(const void* tab, PatchGrid g, T scale, const T* x, const T* b, T* bc,
@@ -3928,7 +3922,7 @@ KernelSet<T> make_set() {
   k.smooth[11] = &launch_smooth<T, 11>;
   k.smooth_split = (kSplitOK || kOnePatchShape) ? 1 : 0;
   k.smooth_hi_full = kOnePatchShape ? 1 : 0;
-  k.smooth_direct = kDirect<1> ? 1 : 0;
+  k.direct_below = kDirect<1> ? direct_below(D, K, sizeof(T)) : 0;
   k.restrict_residual = &launch_restrict<T>;
   k.prolongate_add = &launch_prolong<T>;
   k.coarse = &launch_coarse<T>;
