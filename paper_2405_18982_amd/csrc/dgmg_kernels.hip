@@ -2239,13 +2239,13 @@ __device__ __forceinline__ void gs_body(const Tab<K, T>* __restrict__ t, int N, 
       if (active) {
         const T* xm = x0 - cy - NC;
         if (ROWLDS && H <= 0 && lane < n * n) A[kGsM + lane] = kMassRows<T>.v[lane];
+        // (3-D Q2 has more lines than lanes: all of its loads go first)
+        constexpr int NIT = (8 * E + TPP - 1) / TPP;
+        Line<T> v[NIT];
 #pragma unroll
-        for (int li0 = 0; li0 < 8 * E; li0 += TPP) {
-          const int li = li0 + lane;
-          if (8 * E % TPP != 0 && li >= 8 * E) {
-            if (!TIGHT && li0 == 0) load_b();
-            break;
-          }
+        for (int it = 0; it < NIT; ++it) {
+          const int li = it * TPP + lane;
+          if (8 * E % TPP != 0 && li >= 8 * E) break;
           const int f = small_div<E>(li), i = li - f * E;
           const int in = small_div<n>(i), im = i - in * n;
           const bool xdir = f >= 4, right = (f & 2) != 0;
@@ -2256,12 +2256,18 @@ __device__ __forceinline__ void gs_body(const Tab<K, T>* __restrict__ t, int N, 
           const unsigned kn = (right != trace) ? K : 0;
           const unsigned o = xdir ? cn * NC + kn + (unsigned)(in + 1) * cy + n * im
                                   : cn * cy + n * kn + (unsigned)((in + 1) * NC + im);
-          Line<T> v, w;
 #pragma unroll
-          for (int p = 0; p < E; ++p) v.v[p] = at32(p < n ? xm : xm + lc, o + (p % n) * ln);
-          if (!TIGHT && li0 == 0) load_b();
-          if (WARM && li0 == 0) warm_wait(warm);
-          L1::ms(t, tyl, v, w);
+          for (int p = 0; p < E; ++p) v[it].v[p] = at32(p < n ? xm : xm + lc, o + (p % n) * ln);
+        }
+        if constexpr (!TIGHT) load_b();
+        if constexpr (WARM) warm_wait(warm);
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) {
+          const int li = it * TPP + lane;
+          if (8 * E % TPP != 0 && li >= 8 * E) break;
+          const int f = small_div<E>(li), i = li - f * E;
+          Line<T> w;
+          L1::ms(t, tyl, v[it], w);
           store_coefs<H>(A, f * SZ + i, SY, w);
         }
 #pragma unroll
