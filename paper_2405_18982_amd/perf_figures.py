@@ -87,12 +87,13 @@ def arith(out, k_list=(1, 2, 3, 4, 5, 6, 7), target=2 ** 27):
         ta = _time(lambda: prob.apply(x, out=y), reps=10)
         ts = _time(lambda: prob.smooth(x, b), reps=3)
         ra = roofline.bound(roofline.apply_counts(3, k, N), ta)
-        rs = roofline.bound(roofline.smooth_step_counts(3, k, N), ts)
+        sc = roofline.smooth_run_counts(3, k, N)
+        rs = roofline.bound(sc, ts)
         out({"fig": "arith", "k": k, "L": L, "ndofs": prob.ndofs(),
              "apply_tflops": roofline.apply_counts(3, k, N)["flops"] / ta / 1e12,
              "apply_gbs": roofline.apply_counts(3, k, N)["bytes"] / ta / 1e9, "apply_bound": ra["bound"],
-             "smooth_tflops": roofline.smooth_step_counts(3, k, N)["flops"] / ts / 1e12,
-             "smooth_gbs": roofline.smooth_step_counts(3, k, N)["bytes"] / ts / 1e9,
+             "smooth_tflops": sc["flops"] / ts / 1e12,
+             "smooth_gbs": sc["bytes"] / ts / 1e9,
              "smooth_bound": rs["bound"]})
         prob.close()
         del x, b, y

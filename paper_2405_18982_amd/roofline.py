@@ -8,6 +8,11 @@ count the sum-factorised arithmetic of the method as the kernels evaluate it
 of the face data); the fast-diagonalisation solve counts the minimal
 2 d n_I^(d+1) multiply-adds of the tensor contractions on the kept space
 V_j plus one scaling per kept node.  One multiply-add = 2 flops.
+
+The Dirichlet smoothers have two counts: smooth_step_counts, the step as it is
+stated (a residual by operator passes, then the local solve), and
+smooth_run_counts, the step in the form that runs (takes_direct_form), which is
+what a measured rate is a rate of.
 """
 
 import itertools
@@ -62,9 +67,7 @@ def apply_counts(dim, k, N, nrhs=1, s=8):
 
 def smooth_colour_counts(dim, k, N, colour, nrhs=1, s=8):
     """One colour launch of the smoother on a level with N cells per direction,
-    counted as stated: residual of the patch, then the local solve.  The direct
-    form of the Dirichlet kernels reaches the same values with about half of
-    the operations."""
+    as stated: residual of the patch by operator passes, then the local solve."""
     n = k + 1
     E = 2 * n
     los = patch_los(N, colour, dim)
@@ -86,6 +89,63 @@ def smooth_step_counts(dim, k, N, nrhs=1, s=8):
     tot = dict(bytes=0, flops=0)
     for c in range(2 ** dim):
         r = smooth_colour_counts(dim, k, N, c, nrhs, s)
+        tot["bytes"] += r["bytes"]
+        tot["flops"] += r["flops"]
+    return tot
+
+
+def takes_direct_form(dim, k, N, s=8):
+    """Whether the Dirichlet smoothers solve for the new values directly on a level
+    with N cells per direction (the rules of csrc/dgmg_internal.h)."""
+    if dim == 3:
+        return k >= 2
+    below = (256 if k == 5 else 128) if s == 4 and 4 <= k <= 6 else 1 << 30
+    return k >= 4 and N < below
+
+
+def direct_colour_counts(dim, k, N, colour, nrhs=1, s=8):
+    """One colour launch in direct form, consistent residual: b on V_j and x on the
+    tile's other nodes read, x on V_j written (an outer trace is a dropped layer of
+    the next patch); S^T and S on the kept space, on an interior line by even-odd
+    halves, the couplings of each line to its ends, and the dropped layers and
+    outer traces transformed along their faces."""
+    n = k + 1
+    E = 2 * n
+    nb = madd = add = 0
+    for lo in itertools.product(*patch_los(N, colour, dim)):
+        m = [_n_kept(k, N, l) for l in lo]
+        ends = [E - mi for mi in m]              # dropped ends; a trace beyond each
+        even_odd = [mi == 2 * k for mi in m]     # neither end on the boundary
+        vj = 1
+        for mi in m:
+            vj *= mi
+        nb += s * (E ** dim + vj)
+        for mi, eo in zip(m, even_odd):
+            lines = vj // mi
+            madd += lines * 2 * (mi * mi // 2 if eo else mi * mi)  # S^T and S
+            add += lines * 2 * mi if eo else 0
+            madd += lines * 3 * mi                                 # gp, gt and gm
+        add += vj                                                  # scaling
+
+        def ms(i):  # S^T M of one line along direction i
+            return m[i] * n if even_odd[i] else m[i] * E
+
+        if dim == 3:
+            madd += 2 * ends[2] * 2 * E * E * n                               # z: M_x, M_y
+            madd += 2 * ends[1] * (E * ms(2) + m[2] * E * n)                  # y: S^T M along z, M_x
+            madd += 2 * ends[0] * (E * ms(2) + m[2] * ms(1))                  # x: S^T M along z, y
+        else:
+            madd += 2 * ends[1] * E * n + 2 * ends[0] * m[1] * E
+    return dict(bytes=nrhs * nb, flops=nrhs * (2 * madd + add))
+
+
+def smooth_run_counts(dim, k, N, nrhs=1, s=8):
+    """One smoothing step of the Dirichlet kernels in the form that runs."""
+    if not takes_direct_form(dim, k, N, s):
+        return smooth_step_counts(dim, k, N, nrhs, s)
+    tot = dict(bytes=0, flops=0)
+    for c in range(2 ** dim):
+        r = direct_colour_counts(dim, k, N, c, nrhs, s)
         tot["bytes"] += r["bytes"]
         tot["flops"] += r["flops"]
     return tot
