@@ -11,11 +11,13 @@
 // 1-D line of the patch (all other coordinates fixed), contracts it in
 // registers with the 1-D matrices (wave-uniform operands read through scalar
 // loads from the Tab struct) and hands the result to the next phase through
-// LDS.  The first phase (along x) reads its lines straight from global memory:
-// an x-line of a patch is two contiguous cell rows, and its outside neighbours
-// across the x-faces are the adjacent rows, so x itself never passes through
-// LDS.  Smoothers keep that x-line in registers and finish with another
-// x-phase that writes x + delta back as contiguous rows.
+// LDS.  Operator phases start along x and read their lines straight from global
+// memory: an x-line of a patch is two contiguous cell rows, and its outside
+// neighbours across the x-faces are the adjacent rows, so x itself never passes
+// through LDS.  Smoothers by operator passes keep that x-line in registers and
+// finish with another x-phase that writes x + delta back as contiguous rows; the
+// direct smoothers (gs_body) start from b and end with the new values along the
+// last direction, as the 3-D operator, the restriction and most prolongations end.
 //
 // Operator (Sec. 2.2): on a Cartesian mesh A = sum_i (x)(M .. L_i .. M), with
 // reference matrices (h = 1) and A_h = kappa h^(D-2) A_ref.  The 1-D SIPG
@@ -721,63 +723,58 @@ __device__ __forceinline__ Sides<T> xsides_rows(T sg, bool bl, bool br, const T 
   return sd;
 }
 
-// Side flags and x-face couplings of x-line (py, pz), read from the rows of
-// the outside neighbours.  MODE 0: full operator rows; 1: smoother (only the
-// traces matter, alpha acts on dropped rows); 2: the paper's Dirichlet
-// residual (interior neighbours ignored, consistency term left out).
-template <typename T, int MODE>
+// Side flags of a line with cells lo, lo + 1 of N along it and no data beyond
+template <typename T>
+__device__ __forceinline__ Sides<T> bare_sides(int lo, int N, bool lit) {
+  return Sides<T>{lo == 0, lo + 1 == N - 1, T(0), T(0), T(0), T(0), lit};
+}
+
+// Side flags and x-face couplings of an operator x-line (py, pz), read from the
+// rows of the outside neighbours.
+template <typename T>
 __device__ __forceinline__ Sides<T> xline_sides(const Tab<K, T>* __restrict__ t, const T* __restrict__ x,
                                                 int N, const PatchPos& P, long long row0) {
   const T half = T(0.5);
   const T sg = t->sigma;
-  Sides<T> sd;
-  sd.bl = (P.lo[0] == 0);
-  sd.br = (P.lo[0] + 1 == N - 1);
-  sd.aL = sd.bL = sd.aR = sd.bR = T(0);
-  sd.lit = (MODE == 2);
-  if (MODE != 2) {
-    if (!sd.bl) {
-      const T* r = x + row0 - NC;
-      const T tr = r[K];
-      sd.bL = -half * tr;
-      if (MODE == 0) sd.aL = face_alpha<T, 0>(sg, face_grad<T, 0>([&](int j) { return r[j]; }), tr);
-    }
-    if (!sd.br) {
-      const T* r = x + row0 + 2 * NC;
-      const T tr = r[0];
-      sd.bR = half * tr;
-      if (MODE == 0) sd.aR = face_alpha<T, 1>(sg, face_grad<T, 1>([&](int j) { return r[j]; }), tr);
-    }
+  Sides<T> sd = bare_sides<T>(P.lo[0], N, false);
+  if (!sd.bl) {
+    const T* r = x + row0 - NC;
+    const T tr = r[K];
+    sd.bL = -half * tr;
+    sd.aL = face_alpha<T, 0>(sg, face_grad<T, 0>([&](int j) { return r[j]; }), tr);
+  }
+  if (!sd.br) {
+    const T* r = x + row0 + 2 * NC;
+    const T tr = r[0];
+    sd.bR = half * tr;
+    sd.aR = face_alpha<T, 1>(sg, face_grad<T, 1>([&](int j) { return r[j]; }), tr);
   }
   return sd;
 }
 
-// Raw face data of interior neighbours across y- (and z-) faces.  Entry i
-// enumerates (dir, side, face node f); f = a + E b with (a, b) the tangential
-// patch coordinates in increasing direction order.  NCOMP = 2 stores
-// (alpha, beta), NCOMP = 1 stores beta only (MODE 2 stores zeros).  Layout: ext[(fd * 2 + side) *
-// NCOMP + comp][f] with fd = dir - 1.
-template <typename T, int MODE>
+// Raw face data (alpha, beta) of interior neighbours across y- (and z-) faces for
+// the operator.  Entry i enumerates (dir, side, face node f); f = a + E b with
+// (a, b) the tangential patch coordinates in increasing direction order.  Layout:
+// ext[(fd * 2 + side) * 2 + comp][f] with fd = dir - 1.
+template <typename T>
 __device__ __forceinline__ void gather_ext(const Tab<K, T>* __restrict__ t, const T* __restrict__ x,
                                            int N, const PatchPos& P, int lane, T* ext) {
-  constexpr int NCOMP = (MODE == 0) ? 2 : 1;
-  constexpr int FD0 = (MODE == 0) ? 0 : 1;  // smoothers read y-face traces from global
   const T half = T(0.5);
   const T sg = t->sigma;
-  // a patch face has one node per lane (NF = TPP), so entry block it = (fd -
-  // FD0) * 2 + side holds this lane's face node f = lane: unrolled, direction
-  // and side are compile-time constants of each block
+  // a patch face has one node per lane (NF = TPP), so entry block it = fd * 2 +
+  // side holds this lane's face node f = lane: unrolled, direction and side are
+  // compile-time constants of each block
   static_assert(NF == TPP, "one face node per lane");
 #pragma unroll
-  for (int it = 0; it < (D - 1 - FD0) * 2; ++it) {
+  for (int it = 0; it < (D - 1) * 2; ++it) {
     const int f = lane;
     const int side = it & 1;
-    const int fd = it / 2 + FD0;
+    const int fd = it / 2;
     const int dir = fd + 1;
     const int lod = (dir == 1) ? P.lo[1] : P.lo[2];  // not P.lo[dir]: no scratch copy of P
     const int nb = (side == 0) ? lod - 1 : lod + 2;
     T alpha = T(0), beta = T(0);
-    if (MODE != 2 && nb >= 0 && nb < N) {
+    if (nb >= 0 && nb < N) {
       // neighbour cell and the face node's local coordinates in it (tangential
       // coordinates from (a, b), 0 along dir); named per direction rather than
       // indexed by the runtime dir, which would put the arrays in scratch
@@ -790,18 +787,12 @@ __device__ __forceinline__ void gather_ext(const Tab<K, T>* __restrict__ t, cons
       const long long base = cell_index(N, cx, cy, cz) * NC + ax + n * (ay + n * az);
       const T tr = x[base + (long long)((side == 0) ? K : 0) * strideN];
       beta = (side == 0) ? -half * tr : half * tr;
-      if (MODE == 0) {
-        auto w = [&](int j) { return x[base + (long long)j * strideN]; };
-        alpha = (side == 0) ? face_alpha<T, 0>(sg, face_grad<T, 0>(w), tr)
-                            : face_alpha<T, 1>(sg, face_grad<T, 1>(w), tr);
-      }
+      auto w = [&](int j) { return x[base + (long long)j * strideN]; };
+      alpha = (side == 0) ? face_alpha<T, 0>(sg, face_grad<T, 0>(w), tr)
+                          : face_alpha<T, 1>(sg, face_grad<T, 1>(w), tr);
     }
-    if (NCOMP == 2) {
-      ext[((fd * 2 + side) * 2 + 0) * NF + f] = alpha;
-      ext[((fd * 2 + side) * 2 + 1) * NF + f] = beta;
-    } else {
-      ext[((fd - FD0) * 2 + side) * NF + f] = beta;
-    }
+    ext[((fd * 2 + side) * 2 + 0) * NF + f] = alpha;
+    ext[((fd * 2 + side) * 2 + 1) * NF + f] = beta;
   }
 }
 
@@ -897,21 +888,12 @@ __device__ __forceinline__ T ext_my(const Tab<K, T>* __restrict__ t, const T* ar
 }
 
 // Sides of a y-line (px, pz) (D = 3) or (px) (D = 2): ext_y contracted with M_x.
-template <typename T, int NCOMP>
+template <typename T>
 __device__ __forceinline__ Sides<T> yline_sides(const Tab<K, T>* __restrict__ t, const T* ext,
                                                 int N, const PatchPos& P, int px, int pz) {
-  Sides<T> sd;
-  sd.bl = (P.lo[1] == 0);
-  sd.br = (P.lo[1] + 1 == N - 1);
-  sd.aL = sd.bL = sd.aR = sd.bR = T(0);
-  sd.lit = false;
-  if (NCOMP == 2) {
-    if (!sd.bl) { sd.aL = ext_mx<T>(t, ext + 0 * NF, px, pz); sd.bL = ext_mx<T>(t, ext + 1 * NF, px, pz); }
-    if (!sd.br) { sd.aR = ext_mx<T>(t, ext + 2 * NF, px, pz); sd.bR = ext_mx<T>(t, ext + 3 * NF, px, pz); }
-  } else {
-    if (!sd.bl) sd.bL = ext_mx<T>(t, ext + 0 * NF, px, pz);
-    if (!sd.br) sd.bR = ext_mx<T>(t, ext + 1 * NF, px, pz);
-  }
+  Sides<T> sd = bare_sides<T>(P.lo[1], N, false);
+  if (!sd.bl) { sd.aL = ext_mx<T>(t, ext + 0 * NF, px, pz); sd.bL = ext_mx<T>(t, ext + 1 * NF, px, pz); }
+  if (!sd.br) { sd.aR = ext_mx<T>(t, ext + 2 * NF, px, pz); sd.bR = ext_mx<T>(t, ext + 3 * NF, px, pz); }
   return sd;
 }
 
@@ -946,11 +928,7 @@ __device__ __forceinline__ void yside_load(const T* __restrict__ x, int N, const
 }
 template <typename T, int MODE>
 __device__ __forceinline__ Sides<T> yside_finish(const YSideRaw<T>& y, int N, const PatchPos& P) {
-  Sides<T> sd;
-  sd.bl = (P.lo[1] == 0);
-  sd.br = (P.lo[1] + 1 == N - 1);
-  sd.aL = sd.bL = sd.aR = sd.bR = T(0);
-  sd.lit = (MODE == 2);
+  Sides<T> sd = bare_sides<T>(P.lo[1], N, MODE == 2);
   if (MODE == 2) return sd;
   const T half = T(0.5);
   if (!sd.bl) {
@@ -961,46 +939,15 @@ __device__ __forceinline__ Sides<T> yside_finish(const YSideRaw<T>& y, int N, co
   }
   return sd;
 }
-// The same in one step (loads only the sides that exist, fewer live values).
-template <typename T, int MODE>
-__device__ __forceinline__ Sides<T> yline_sides_global(const Tab<K, T>* __restrict__ t,
-                                                       const T* __restrict__ x, int N,
-                                                       const PatchPos& P, int px, int pz) {
-  Sides<T> sd;
-  sd.bl = (P.lo[1] == 0);
-  sd.br = (P.lo[1] + 1 == N - 1);
-  sd.aL = sd.bL = sd.aR = sd.bR = T(0);
-  sd.lit = (MODE == 2);
-  if (MODE == 2) return sd;
-  const int cx = P.lo[0] + px / n;
-  const int cz = (D == 3) ? P.lo[2] + pz / n : 0;
-  const int az = (D == 3) ? pz % n : 0;
-  const T half = T(0.5);
-  T row[n];
-  if (!sd.bl || !sd.br) face_row<T>(px % n, row);
-  if (!sd.bl) {
-    const T* r = x + cell_index(N, cx, P.lo[1] - 1, cz) * NC + K * n + az * n * n;
-    sd.bL = -half * face_dot<T>(row, [&](int nu) { return r[nu]; });
-  }
-  if (!sd.br) {
-    const T* r = x + cell_index(N, cx, P.lo[1] + 2, cz) * NC + az * n * n;
-    sd.bR = half * face_dot<T>(row, [&](int nu) { return r[nu]; });
-  }
-  return sd;
-}
 
-// In the y-phase the z-face arrays are contracted along x in place (lines at
-// fixed py); in the z-phase the value at (px, py) is contracted along y.
-// z-face arrays follow the y-face arrays in the operator layout; smoothers
-// keep only the z-face traces in LDS.
-template <int NCOMP>
-__device__ __forceinline__ constexpr int extz_base() { return NCOMP == 2 ? 4 * NF : 0; }
-
-template <typename T, int NCOMP>
+// In the y-phase the z-face arrays (after the y-face arrays) are contracted along
+// x in place (lines at fixed py); in the z-phase the value at (px, py) is
+// contracted along y.
+template <typename T>
 __device__ __forceinline__ void extz_mass_x_line(const Tab<K, T>* __restrict__ t, T* ext, int j) {
   const int py = j % E;
-  const int arr = j / E;  // (side * NCOMP + comp)
-  T* a = ext + extz_base<NCOMP>() + arr * NF + py * E;
+  const int arr = j / E;  // (side * 2 + comp)
+  T* a = ext + 4 * NF + arr * NF + py * E;
   T v[E];
 #pragma unroll
   for (int p = 0; p < E; ++p) v[p] = a[p];
@@ -1016,22 +963,13 @@ __device__ __forceinline__ void extz_mass_x_line(const Tab<K, T>* __restrict__ t
       a[c * n + mu] = face_dot<T>(row, [&](int nu) { return v[c * n + nu]; });
     }
 }
-template <typename T, int NCOMP>
+template <typename T>
 __device__ __forceinline__ Sides<T> zline_sides(const Tab<K, T>* __restrict__ t, const T* ext,
                                                 int N, const PatchPos& P, int px, int py) {
-  Sides<T> sd;
-  sd.bl = (P.lo[2] == 0);
-  sd.br = (P.lo[2] + 1 == N - 1);
-  sd.aL = sd.bL = sd.aR = sd.bR = T(0);
-  sd.lit = false;
-  const T* z = ext + extz_base<NCOMP>();
-  if (NCOMP == 2) {
-    if (!sd.bl) { sd.aL = ext_my<T>(t, z + 0 * NF, px, py); sd.bL = ext_my<T>(t, z + 1 * NF, px, py); }
-    if (!sd.br) { sd.aR = ext_my<T>(t, z + 2 * NF, px, py); sd.bR = ext_my<T>(t, z + 3 * NF, px, py); }
-  } else {
-    if (!sd.bl) sd.bL = ext_my<T>(t, z + 0 * NF, px, py);
-    if (!sd.br) sd.bR = ext_my<T>(t, z + 1 * NF, px, py);
-  }
+  Sides<T> sd = bare_sides<T>(P.lo[2], N, false);
+  const T* z = ext + 4 * NF;
+  if (!sd.bl) { sd.aL = ext_my<T>(t, z + 0 * NF, px, py); sd.bL = ext_my<T>(t, z + 1 * NF, px, py); }
+  if (!sd.br) { sd.aR = ext_my<T>(t, z + 2 * NF, px, py); sd.bR = ext_my<T>(t, z + 3 * NF, px, py); }
   return sd;
 }
 
@@ -1109,37 +1047,10 @@ __device__ __forceinline__ T xcontract_lanes(const T (&row)[n], T v) {
 // Dirichlet smoothers' z-face traces in registers (patches of one wave): lane
 // (px, py) holds the traces of its x-block on each z-neighbour contracted with
 // its mass row (operator_passes), and the z-line (px, py = lane / E) contracts
-// them along y across lanes. TRACES false: no neighbour data
-template <typename T, bool TRACES>
-__device__ __forceinline__ Sides<T> rfz_sides(int N, const PatchPos& P, int lane, T wz0, T wz1) {
-  Sides<T> sd;
-  sd.bl = (P.lo[2] == 0);
-  sd.br = (P.lo[2] + 1 == N - 1);
-  sd.aL = sd.bL = sd.aR = sd.bR = T(0);
-  sd.lit = false;
-  if constexpr (TRACES) {
-    const int py = lane / E;
-    T rowy[n];
-    face_row<T>(py % n, rowy);
-    const int wl = threadIdx.x & 63;
-    const T zL = ycontract_lanes<T>(rowy, wz0, wl, py % n);
-    const T zR = ycontract_lanes<T>(rowy, wz1, wl, py % n);
-    if (!sd.bl) sd.bL = zL;
-    if (!sd.br) sd.bR = zR;
-  }
-  return sd;
-}
-
-// rfz_sides with traces, the mass row of py = lane / E given (loaded by the
-// caller with its other global loads); same arithmetic
+// them along y across lanes; rowy: the mass row of py
 template <typename T>
-__device__ __forceinline__ Sides<T> rfz_sides_row(const T (&rowy)[n], int N, const PatchPos& P, int lane, T wz0,
-                                                  T wz1) {
-  Sides<T> sd;
-  sd.bl = (P.lo[2] == 0);
-  sd.br = (P.lo[2] + 1 == N - 1);
-  sd.aL = sd.bL = sd.aR = sd.bR = T(0);
-  sd.lit = false;
+__device__ __forceinline__ Sides<T> rfz_sides(const T (&rowy)[n], int N, const PatchPos& P, int lane, T wz0, T wz1) {
+  Sides<T> sd = bare_sides<T>(P.lo[2], N, false);
   const int py = lane / E;
   const int wl = threadIdx.x & 63;
   const T zL = ycontract_lanes<T>(rowy, wz0, wl, py % n);
@@ -1159,13 +1070,12 @@ template <typename T, int MODE, bool RFA = false, typename Emit>
 __device__ __forceinline__ void operator_passes(const Tab<K, T>* __restrict__ t, const T* __restrict__ x,
                                                 int N, const PatchPos& P, T* A, T* B, T* ext,
                                                 int lane, bool active, Line<T>& xl, Emit emit) {
-  constexpr int NCOMP = (MODE == 0) ? 2 : 1;
-  // Dirichlet smoothers on patches of one wave: the z-face traces go through
-  // registers, not LDS.  Lane (px, py) reads the n traces of its x-block on
-  // each z-neighbour and contracts beta = -+t/2 with its mass row (as
-  // gather_ext + extz_mass_x_line), the Z pass contracts along y across lanes
-  // (as ext_my): the same values, no extra pass over the face arrays.
-  constexpr bool RFZ = (D == 3) && kZShfl && (MODE == 1 || MODE == 2);
+  // The Dirichlet residual with z-face traces (3-D Q1, a patch within a wave): these go
+  // through registers.  Lane (px, py) reads the n traces of its x-block on each
+  // z-neighbour and contracts beta = -+t/2 with its mass row, the Z pass contracts
+  // along y across lanes.
+  constexpr bool RFZ = (D == 3) && MODE == 1;
+  static_assert(!RFZ || kZShfl, "patches of several waves take the direct form");
   static_assert(!RFA || (MODE == 0 && D == 3 && kZShfl), "register face data: 3-D operator, one wave");
   T wz0 = T(0), wz1 = T(0);
   T ya0 = T(0), yb0 = T(0), ya1 = T(0), yb1 = T(0);  // RFA: y-line (px, pz) = (lane % E, lane / E)
@@ -1181,16 +1091,15 @@ __device__ __forceinline__ void operator_passes(const Tab<K, T>* __restrict__ t,
   Sides<T> ysd_global{};
   T rowz[n];
   // X0: a = M_x x -> A, b = L_x x -> B
-  if (active && MODE != 0 && NL == TPP) {
-    // Smoothers with one line per lane: every global load of the pass is
+  if (MODE != 0 && active) {
+    // Smoothers: every global load of the pass is
     // issued before any of the values is used (one memory round trip instead
-    // of one per helper), then the arithmetic of yline_sides_global,
-    // rfz_traces and xline_sides in their order.
+    // of one per helper), then the arithmetic
     const int px = lane % E, q = lane / E;  // y-line (px, pz = q), z-face node (px, py = q)
     YSideRaw<T> yraw;
     yside_load<T, MODE>(x, N, P, px, (D == 3) ? q : 0, yraw);
     T zl[n], zr[n];
-    if constexpr (RFZ && MODE == 1) {
+    if constexpr (RFZ) {
       const int cx = P.lo[0] + px / n, cy = P.lo[1] + q / n;
       const long long o = (long long)n * (q % n);
       const T* cl = x + cell_index(N, cx, cy, P.lo[2] > 0 ? P.lo[2] - 1 : P.lo[2]) * NC + o + K * n * n;
@@ -1202,8 +1111,6 @@ __device__ __forceinline__ void operator_passes(const Tab<K, T>* __restrict__ t,
       }
       face_row<T>(q % n, rowz);
     }
-    // (patches of several waves take the z-face traces in the direct form only)
-    static_assert(D == 2 || RFZ || MODE != 1, "operator passes with z-traces: one-wave patches");
     const int py = lane % E, pz = lane / E;
     const long long row0 = xrow_offset(N, P, py, pz);
     read_xline<T>(x, row0, xl);
@@ -1214,7 +1121,7 @@ __device__ __forceinline__ void operator_passes(const Tab<K, T>* __restrict__ t,
       xtr = x[xbr ? row0 : row0 + 2 * NC];
     }
     ysd_global = yside_finish<T, MODE>(yraw, N, P);
-    if constexpr (RFZ && MODE == 1) {
+    if constexpr (RFZ) {
       const T half = T(0.5);
       if (P.lo[2] > 0) {
         T s = T(0);
@@ -1228,15 +1135,8 @@ __device__ __forceinline__ void operator_passes(const Tab<K, T>* __restrict__ t,
         for (int nu = 0; nu < n; ++nu) s += yraw.row[nu] * (half * zr[nu]);
         wz1 = s;
       }
-    } else if constexpr (!RFZ && D == 3) {
-      ext[lane] = T(0);  // MODE 2: no z-face traces
-      ext[NF + lane] = T(0);
     }
-    Sides<T> sd;
-    sd.bl = xbl;
-    sd.br = xbr;
-    sd.aL = sd.bL = sd.aR = sd.bR = T(0);
-    sd.lit = (MODE == 2);
+    Sides<T> sd = bare_sides<T>(P.lo[0], N, MODE == 2);
     if (MODE != 2) {
       if (!sd.bl) sd.bL = -T(0.5) * xtl;
       if (!sd.br) sd.bR = T(0.5) * xtr;
@@ -1249,7 +1149,7 @@ __device__ __forceinline__ void operator_passes(const Tab<K, T>* __restrict__ t,
     store_line(A, base, stride, a);
     store_line(B, base, stride, b);
   } else if (RFA && active) {
-      static_assert(!RFA || kFaceDPP, "x-blocks within a quad");
+    static_assert(!RFA || kFaceDPP, "x-blocks within a quad");
     // register face data (operator, patches of one wave): every global load
     // first, as in k_apply_rf -- this lane's node column of each neighbour
     // face block, the x-line and its x-neighbours' rows -- then the per-node
@@ -1322,28 +1222,25 @@ __device__ __forceinline__ void operator_passes(const Tab<K, T>* __restrict__ t,
     if (!zbl) { za0 = sza0; zb0 = szb0; }
     if (!zbr) { za1 = sza1; zb1 = szb1; }
   } else if (active) {
-    gather_ext<T, MODE>(t, x, N, P, lane, ext);
-    for (int i = lane; i < NL; i += TPP) {
-      const int py = i % E, pz = i / E;
-      const long long row0 = xrow_offset(N, P, py, pz);
-      read_xline<T>(x, row0, xl);
-      const Sides<T> sd = xline_sides<T, MODE>(t, x, N, P, row0);
-      int base, stride;
-      line_geom(0, i, base, stride);
-      Line<T> a, b;
-      line_mass<T>(t, xl, a, n0x, nEx);
-      line_sipg<T, false>(t, xl, sd, b, n0x, nEx);
-      store_line(A, base, stride, a);
-      store_line(B, base, stride, b);
-    }
+    gather_ext<T>(t, x, N, P, lane, ext);
+    const long long row0 = xrow_offset(N, P, lane % E, lane / E);
+    read_xline<T>(x, row0, xl);
+    const Sides<T> sd = xline_sides<T>(t, x, N, P, row0);
+    int base, stride;
+    line_geom(0, lane, base, stride);
+    Line<T> a, b;
+    line_mass<T>(t, xl, a, n0x, nEx);
+    line_sipg<T, false>(t, xl, sd, b, n0x, nEx);
+    store_line(A, base, stride, a);
+    store_line(B, base, stride, b);
   }
   __syncthreads();
   if constexpr (D == 3) {
     // Y: c = M_y b + L_y a -> B, d = M_y a -> A; z-face data contracted along x
     if (active) {
-      // one y-line per lane (NL = TPP), then, without register face data,
-      // lanes 0 .. 2 NCOMP E - 1 contract one z-face row each along x (the
-      // z-face arrays; the y-lines read only the y-face arrays of ext)
+      // one y-line per lane, then, for face data in LDS, lanes 0 .. 4 E - 1
+      // contract one z-face row each along x (the y-lines read only the y-face
+      // arrays of ext)
       {
         const int i = lane;
         {
@@ -1363,7 +1260,7 @@ __device__ __forceinline__ void operator_passes(const Tab<K, T>* __restrict__ t,
             sd.bR = yb1;
             sd.lit = false;
           } else {
-            sd = (MODE == 0) ? yline_sides<T, NCOMP>(t, ext, N, P, px, pz) : ysd_global;
+            sd = (MODE == 0) ? yline_sides<T>(t, ext, N, P, px, pz) : ysd_global;
           }
           line_mass<T>(t, b, c, n0y, nEy);
           line_sipg<T, true>(t, a, sd, c, n0y, nEy);
@@ -1372,8 +1269,8 @@ __device__ __forceinline__ void operator_passes(const Tab<K, T>* __restrict__ t,
           store_line(A, base, stride, d);
         }
       }
-      if constexpr (!(RFZ || RFA))
-        if (lane < 2 * NCOMP * E) extz_mass_x_line<T, NCOMP>(t, ext, lane);
+      if constexpr (MODE == 0 && !RFA)
+        if (lane < 4 * E) extz_mass_x_line<T>(t, ext, lane);
     }
     __syncthreads();
     // Z: y = M_z c + L_z d
@@ -1386,10 +1283,10 @@ __device__ __forceinline__ void operator_passes(const Tab<K, T>* __restrict__ t,
         load_line(B, base, stride, c);
         load_line(A, base, stride, d);
         Sides<T> sd;
-        if constexpr (RFZ && MODE == 1 && NL == TPP) {
-          sd = rfz_sides_row<T>(rowz, N, P, i, wz0, wz1);
-        } else if constexpr (RFZ) {
-          sd = rfz_sides<T, MODE == 1>(N, P, i, wz0, wz1);
+        if constexpr (RFZ) {
+          sd = rfz_sides<T>(rowz, N, P, i, wz0, wz1);
+        } else if constexpr (MODE == 2) {
+          sd = bare_sides<T>(P.lo[2], N, true);
         } else if constexpr (RFA) {
           const int wl = threadIdx.x & 63;
           const T zaL = ycontract_lanes<T>(rowz, za0, wl, py % n);
@@ -1404,9 +1301,8 @@ __device__ __forceinline__ void operator_passes(const Tab<K, T>* __restrict__ t,
           sd.bR = sd.br ? T(0) : zbR;
           sd.lit = false;
         } else {
-          sd = zline_sides<T, NCOMP>(t, ext, N, P, px, py);
+          sd = zline_sides<T>(t, ext, N, P, px, py);
         }
-        sd.lit = (MODE == 2);
         line_mass<T>(t, c, y, n0z, nEz);
         line_sipg<T, true>(t, d, sd, y, n0z, nEz);
         emit(i, base, stride, y);
@@ -1422,7 +1318,7 @@ __device__ __forceinline__ void operator_passes(const Tab<K, T>* __restrict__ t,
         Line<T> a, b, y;
         load_line(A, base, stride, a);
         load_line(B, base, stride, b);
-        const Sides<T> sd = (MODE == 0) ? yline_sides<T, NCOMP>(t, ext, N, P, px, 0) : ysd_global;
+        const Sides<T> sd = (MODE == 0) ? yline_sides<T>(t, ext, N, P, px, 0) : ysd_global;
         line_mass<T>(t, b, y, n0y, nEy);
         line_sipg<T, true>(t, a, sd, y, n0y, nEy);
         emit(i, base, stride, y);
@@ -1871,7 +1767,7 @@ template <int MODE, typename T = double>
 __host__ __device__ constexpr int smooth_pp() {
   return kDirect<MODE> ? kGsPP
          : MODE == 3 ? (kFullRF ? 2 * TS : kFullOnApplyRF ? kApplyRFPP<T> : Smem<2, (D - 1) * 2 * 2 * NF>::per_patch)
-                   : Smem<2, (D - 2) * 2 * NF>::per_patch;
+                   : 2 * TS;
 }
 
 // ------------------------------------- Dirichlet smoothers, direct form
@@ -2838,16 +2734,6 @@ template <typename T, int TY, int SP, int H>
 __device__ __forceinline__ void half_St_t(const Tab<K, T>* __restrict__ t, const Line<T>& v, Half<T>& o) {
   using B = FDB<SP, TY>;
   const Coef<T> S = pass_coef<T, kOpaqueFD<T, SP>>(fd_S<T, SP>(t, TY));
-  if constexpr (kEO && SP == SP_DIR && TY == 0) {
-    T vp[kEOH], vm[kEOH];
-    eo_split<T>(v, vp, vm);
-#pragma unroll
-    for (int j = 0; j < n; ++j) {
-      const int q = H * n + j;
-      o.v[j] = (q < 2 * kEOH) ? eo_coef<T>(S, vp, vm, q) : T(0);
-    }
-    return;
-  }
 #pragma unroll
   for (int j = 0; j < n; ++j) {
     const int q = H * n + j;
@@ -2864,21 +2750,6 @@ template <typename T, int TY, int SP, int H>
 __device__ __forceinline__ void half_S_t(const Tab<K, T>* __restrict__ t, const Line<T>& v, Half<T>& o) {
   using B = FDB<SP, TY>;
   const Coef<T> S = pass_coef<T, kOpaqueFD<T, SP>>(fd_S<T, SP>(t, TY));
-  if constexpr (kEO && SP == SP_DIR && TY == 0) {
-#pragma unroll
-    for (int j = 0; j < n; ++j) {
-      const int p = H * n + j;
-      if (p == 0 || p == E - 1) {
-        o.v[j] = T(0);
-      } else {
-        const int k = (p <= kEOH) ? p - 1 : E - 2 - p;
-        T e, d;
-        eo_pair<T>(S, v, k, e, d);
-        o.v[j] = (p <= kEOH) ? e + d : e - d;
-      }
-    }
-    return;
-  }
 #pragma unroll
   for (int j = 0; j < n; ++j) {
     const int p = H * n + j;
@@ -2964,14 +2835,12 @@ __device__ __forceinline__ void smooth_split_body(const Tab<K, T>* __restrict__ 
   } else {
     // the clamped residual reads the patch cells alone: no traces of the
     // neighbours, the sides only say where the domain boundary is
-    Sides<T> ysd{}, sd{};
+    const Sides<T> sd = bare_sides<T>(P.lo[0], g.N, true), ysd = bare_sides<T>(P.lo[1], g.N, true);
     Line<T> xl;
     const int py = lane % E, pz = lane / E;
     const long long row0 = xrow_offset(g.N, P, py, pz);
     if (active) {
-      ysd = yline_sides_global<T, 2>(t, xr, g.N, P, lane % E, lane / E);
       read_xline<T>(xr, row0, xl);
-      sd = xline_sides<T, 2>(t, xr, g.N, P, row0);
     }
     // X0: a = M_x x, b = L_x x on this half -> A, B
     if (active) {
@@ -3011,7 +2880,7 @@ __device__ __forceinline__ void smooth_split_body(const Tab<K, T>* __restrict__ 
       Line<T> cl, dl;
       load_line(B, base, stride, cl);
       load_line(A, base, stride, dl);
-      const Sides<T> zsd{P.lo[2] == 0, P.lo[2] + 1 == g.N - 1, T(0), T(0), T(0), T(0), true};
+      const Sides<T> zsd = bare_sides<T>(P.lo[2], g.N, true);
       Half<T> y;
       half_mass<T, H>(cl, y, endz);
       half_sipg<T, H, true>(t, dl, zsd, y, endz);
