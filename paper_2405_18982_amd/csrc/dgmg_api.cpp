@@ -1404,16 +1404,24 @@ dgmg_status tune_kernel(dgmg_ctx* c, int nrhs, bool smooth, int level, T* x, T* 
   // candidate shapes; those that would repeat another are left out
   std::vector<int> shapes;
   const KernelSet<T>& ks = kset<T>(c);
-  const bool rpack = nrhs > 1 && (smooth ? ks.smooth_rpack[c->variant] > 1 : ks.apply_rpack != 0);
   if (smooth) {
-    const bool hi = c->variant == DGMG_SMOOTH_FULL ? ks.smooth_hi_full : ks.smooth_split;
+    const bool split = ks.smooth_split && c->variant != DGMG_SMOOTH_FULL;
     const bool direct = c->lv[level].N < ks.direct_below && (c->variant == DGMG_SMOOTH_EXACT || c->variant == DGMG_SMOOTH_LOCAL);
-    for (int v = 0; v < 12; ++v)
-      if ((v < 8 ? v < 4 || hi : rpack) && !(direct && (v & 2))) shapes.push_back(v);
+    const int slots = nrhs > 1 ? ks.smooth_rpack[c->variant] : 1;
+    for (int v = 0; v < 12; ++v) {
+      const bool odd = v & 1;
+      if ((v & 2) && direct) continue;  // one order of loads
+      if (v < 4 ? odd && !ks.two_counts
+                : v < 8 ? !(ks.one_patch ? !odd : split && (!odd || ks.two_counts))
+                        : slots < (odd ? 2 : 4))  // the smaller count is half of slots
+        continue;
+      shapes.push_back(v);
+    }
   } else {
-    shapes = {0, 1};
+    shapes = {0};
+    if (ks.two_counts) shapes.push_back(1);
     if (ks.apply_rf) shapes.push_back(2);
-    if (rpack) shapes.push_back(3);
+    if (nrhs > 1 && ks.apply_rpack) shapes.push_back(3);
   }
   const int reps = smooth ? 3 : 20;
   hipEvent_t e0, e1;

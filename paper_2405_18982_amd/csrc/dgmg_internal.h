@@ -126,6 +126,8 @@ struct KernelSet {
   // the smoother also whether b is prefetched)
   hipError_t (*apply[kApplyShapes])(const void* tab, PatchGrid g, T scale, const T* x, T* y, int nrhs,
                          long long ndof, hipStream_t s);
+  // 1 where bit 0 of the shapes (more patches per workgroup) changes anything
+  int two_counts;
   // 1 where apply shape 2 (face data in registers) differs from shape 0
   int apply_rf;
   // 1 where the right-hand-side-packed apply (shape 3) holds more than one slot
@@ -141,11 +143,11 @@ struct KernelSet {
   hipError_t (*smooth[kSmoothShapes])(const void* tab, PatchGrid g, T scale, T inv_scale, int variant,
                           int zero, const T* xin, T* xout, const T* b, int nrhs, long long ndof,
                           hipStream_t s);
-  // 1 where shapes 4..7 (two waves per patch, or one patch per workgroup
-  // where patches share a wave) differ from 0..3; smooth_hi_full: also for
-  // the Full kernel
+  // 1 where smoother shapes 4..7 are one patch per workgroup (patches share a
+  // wave otherwise), or two waves per patch (not the Full kernel); else they are
+  // 0..3 again
+  int one_patch;
   int smooth_split;
-  int smooth_hi_full;
   // levels with fewer cells a direction take the direct form of the Dirichlet
   // smoothers, which has no prefetch shapes (0: none)
   int direct_below;

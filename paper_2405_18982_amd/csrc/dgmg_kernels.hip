@@ -3472,7 +3472,10 @@ k_bottom3(const Tab<K, T>* __restrict__ t, Bottom3Args<T> a3) {
 // and 2^D two-wave slots fit one workgroup: 3-D Q3): waves 2s and 2s + 1 form
 // patch slot s, and the transfer and coarse stages run on the even waves while
 // the odd ones meet the barriers only.  The split smoothing body gives every
-// output bit for bit as the one-wave body.
+// output bit for bit as the one-wave body.  Clamped kernel only: the direct form
+// is faster with one wave here (V-cycle on 4^3 cells, two waves / one: FP64 119 / 91 us,
+// FP32 74 / 66), its halves being code of their own that one workgroup fetches for
+// every stage.
 constexpr bool kBottomSplitOK = kSplitOK && 2 * TPP * kBottomSlots <= 1024;
 
 template <typename T, int MODE, bool ZERO>
@@ -3776,6 +3779,8 @@ KernelSet<T> make_set() {
   k.apply[1] = &launch_apply<T, 1>;
   k.apply[2] = &launch_apply_rf<T>;
   k.apply[3] = &launch_apply_rpack<T>;
+  k.two_counts = Shape<1>::PPB != Shape<0>::PPB ? 1 : 0;
+  k.one_patch = kOnePatchShape ? 1 : 0;
   k.apply_rf = kApplyRF ? 1 : 0;
   k.apply_rpack = rpack_apply_slots<T>() > 1 ? 1 : 0;
   k.smooth_rpack[0] = rpack_smooth_slots<T, 1>(true);
@@ -3795,8 +3800,7 @@ KernelSet<T> make_set() {
   k.smooth[9] = &launch_smooth<T, 9>;
   k.smooth[10] = &launch_smooth<T, 10>;
   k.smooth[11] = &launch_smooth<T, 11>;
-  k.smooth_split = (kSplitOK || kOnePatchShape) ? 1 : 0;
-  k.smooth_hi_full = kOnePatchShape ? 1 : 0;
+  k.smooth_split = kSplitOK ? 1 : 0;
   k.direct_below = kDirect<1> ? direct_below(D, K, sizeof(T)) : 0;
   k.restrict_residual = &launch_restrict<T>;
   k.prolongate_add = &launch_prolong<T>;
