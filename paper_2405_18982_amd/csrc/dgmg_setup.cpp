@@ -126,22 +126,24 @@ void jacobi_eigen(const std::vector<Real>& A, int m, std::vector<Real>& w, std::
 bool basis_eigenpairs(const std::vector<Real>& L, const std::vector<Real>& Mp, int E,
                       const std::vector<Real>& Cb, int m, std::vector<double>& Sout,
                       std::vector<double>& lamout, const char** err) {
-  std::vector<Real> Lt(m * m), Mt(m * m), LC(E * m, 0), MC(E * m, 0);
-  for (int p = 0; p < E; ++p)
-    for (int q = 0; q < E; ++q)
-      for (int j = 0; j < m; ++j) {
-        LC[p * m + j] += L[p * E + q] * Cb[q * m + j];
-        MC[p * m + j] += Mp[p * E + q] * Cb[q * m + j];
-      }
-  for (int i = 0; i < m; ++i)
+  std::vector<Real> Lt(m * m, 0), Mt(m * m, 0), LC(E * m, 0), MC(E * m, 0);
+  for (int q = 0; q < E; ++q)  // (few entries of Cb differ from zero)
     for (int j = 0; j < m; ++j) {
-      Real sl = 0, sm = 0;
+      const Real c = Cb[q * m + j];
+      if (c == 0) continue;
       for (int p = 0; p < E; ++p) {
-        sl += Cb[p * m + i] * LC[p * m + j];
-        sm += Cb[p * m + i] * MC[p * m + j];
+        LC[p * m + j] += L[p * E + q] * c;
+        MC[p * m + j] += Mp[p * E + q] * c;
       }
-      Lt[i * m + j] = sl;
-      Mt[i * m + j] = sm;
+    }
+  for (int p = 0; p < E; ++p)
+    for (int i = 0; i < m; ++i) {
+      const Real c = Cb[p * m + i];
+      if (c == 0) continue;
+      for (int j = 0; j < m; ++j) {
+        Lt[i * m + j] += c * LC[p * m + j];
+        Mt[i * m + j] += c * MC[p * m + j];
+      }
     }
   std::vector<Real> C;
   if (!cholesky(Mt, m, C)) { *err = "patch mass matrix is not positive definite"; return false; }
@@ -375,6 +377,13 @@ bool build_host_tables(int k, double sigma, HostTables& T, const char** err) {
       if (!patch_eigenpairs(L, Mp, E, keep, T.S[t], T.lam[t], err)) return false;
     }
     line_couplings(t, L, Mp, T);
+    if (t == 3 && k >= 2) {  // no end on an interior face: the three spaces are one
+      T.Sf[t] = T.S[t];
+      T.lamf[t] = T.lam[t];
+      T.Sc[t] = T.S[t];
+      T.lamc[t] = T.lam[t];
+      continue;
+    }
     // Full kernel: every node of the two cells
     std::vector<int> all(E);
     for (int p = 0; p < E; ++p) all[p] = p;
