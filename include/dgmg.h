@@ -159,8 +159,10 @@ dgmg_status dgmg_apply_mass(dgmg_ctx* ctx, int level, const double* x, double* y
  * fast diagonalisation (Sec. 3.2, eqs. inverse2d/inverse3d/fast_inverse).
  * With the Dirichlet kernels V_j drops the patch-boundary nodes on interior
  * mesh faces and keeps those on the domain boundary; with the Full kernel it
- * is the whole patch (see DGMG_SMOOTH_FULL).  x, b: device [nrhs][ndofs(l)],
- * not overlapping.  1 <= level <= L. */
+ * is the whole patch (see DGMG_SMOOTH_FULL).  A NaN or an infinity in x or b
+ * leaves no finite value in the patches that hold it, also where the new values
+ * are solved for without the old ones.  x, b: device [nrhs][ndofs(l)], not
+ * overlapping.  1 <= level <= L. */
 dgmg_status dgmg_smooth_patch(dgmg_ctx* ctx, int level, double* x, const double* b,
                               int reverse_colours, int nrhs);
 dgmg_status dgmg_smooth_patch_f32(dgmg_ctx* ctx, int level, float* x, const float* b,

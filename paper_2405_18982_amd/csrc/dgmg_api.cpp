@@ -1330,7 +1330,7 @@ namespace {
 // Times every workgroup shape x XCD numbering of apply and smooth on the
 // finest level with HIP events (best of three batches) and keeps the fastest.
 // Results are cached in a JSON object, one entry per line:
-//   "gfx950/d3/k3/L4/nrhs16/fp64/smooth/l4/v0": {"shape": 0, "remap": 1, "us": 16.50, "rev": 2},
+//   "gfx950/d3/k3/L4/nrhs16/fp64/smooth/l4/v0": {"shape": 0, "remap": 1, "us": 16.50, "rev": 3},
 // v0: the smoother variant the entry was timed with (none for the apply, which all
 // share); rev: kTuneRev of the library that timed it, outside which it is timed
 // again.  Entries without both (written by hand, or before there were any) hold for
@@ -1345,7 +1345,7 @@ std::string tune_key(const dgmg_ctx* c, int nrhs, int prec, const char* kernel) 
 
 // Raised whenever a shape comes to mean another kernel, so that timings of the
 // former one are not kept.
-constexpr int kTuneRev = 2;
+constexpr int kTuneRev = 3;
 
 struct CacheEntry {
   std::string key;

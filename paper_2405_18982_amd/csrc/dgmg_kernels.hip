@@ -232,7 +232,8 @@ struct Sides {
 // are off by 2e-7..7e-7 (on differences 2e-7..5e-7) and whose FP32 operator is
 // 3-6% faster on them (3-D Q3 8^3 4.13 / 4.39 us, 32^3 8.1 / 8.4 us, Q1 64^3
 // restriction 11.1 / 11.8 us); 2-D Q2, Q3 would be off by up to 1.6e-6.  FP64
-// keeps the plain rows.
+// keeps the plain rows.  One apply on random values is off by 2-7% more on
+// differences, for their own rounding (3-D Q5 9.7e-8 / 9.3e-8).
 template <typename T>
 constexpr bool kDiff = sizeof(T) == 4 && K >= (D == 3 ? 4 : 2);
 
@@ -2586,7 +2587,7 @@ __device__ __forceinline__ void smooth_body(const Tab<K, T>* __restrict__ t, con
 
 // Waves per SIMD the register allocation of k_smooth aims at (1: no aim): for
 // the direct form in 3-D the most an interior patch's passes allow without
-// spilled vector registers (scalar ones spill to vector lanes: 99 for Q3 FP64, 121 for
+// spilled vector registers (scalar ones spill to vector lanes: 95 for Q3 FP64, 121 for
 // Q7 FP32).
 template <typename T, int MODE, int THREADS, bool GUARD>
 constexpr int smooth_waves() {
